@@ -14,6 +14,7 @@ namespace scdg {
 constexpr int kNvar = 5;
 constexpr int kMaxOrder = 7;
 constexpr int kGjOuter = 128;        // outer panel width of the blocked Gauss-Jordan inverse
+constexpr int kDensePanel = 64;       // panel width of the dense LU of S
 constexpr int kGjAutoBlocked = 320;  // automatic choice: blocked form above this n_i
 
 // One GEMM problem of a batched launch: C = alpha A B + beta C, row-major with
@@ -217,8 +218,14 @@ struct Plan {
   int gj_cfg = -1;                 // tile configuration the lists were built for
 
   // dense S path
-  double *s_dense = nullptr;
-  int32_t *s_piv = nullptr;
+  double *s_dense = nullptr;       // [n1 * n1] LU of the row-scaled S
+  double *dl_scale = nullptr;      // [n1] row scales (powers of two)
+  int32_t *dl_perm = nullptr;      // [n1] row of S at each position of the LU
+  double *dl_lbuf = nullptr;       // [2 n1 * kDensePanel] multipliers of the two panels of a pair
+  double *dl_blk = nullptr;        // [kDensePanel^2 + 2048] LU of a diagonal block, in pivot order, and inverses
+  int32_t *dl_state = nullptr;     // [kDensePanel + 1] its row exchanges, and whether they are swaps
+  double *dl_x = nullptr;          // [2 n1] work vectors of the triangular solves
+  GemmDesc *d_dense_desc = nullptr;  // updates of each pair of panels
   int32_t *d_dense_info = nullptr;
   bool dense_factored = false;
 
@@ -377,8 +384,7 @@ scdg_status dg_jacobian_blocks_on(scdg_dg *dg, const JacPlanView &v, const doubl
 
 // dense path
 hipError_t launch_dense_assemble(const Plan &p, double *s_dense);
-hipError_t launch_dense_lu(Plan &p, double *a, int32_t n, int32_t *piv, int32_t *info);
-hipError_t launch_dense_solve(const double *lu, int32_t n, const int32_t *piv, double *x,
-                              hipStream_t s);
+hipError_t launch_dense_lu(Plan &p);
+hipError_t launch_dense_solve(Plan &p, const double *b, double *x);
 
 }  // namespace scdg

@@ -395,33 +395,6 @@ struct GjRes {
   }
 };
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_mov(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ double read_lane(double v, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                          __builtin_amdgcn_readlane(__double2loint(v), l));
-}
-__device__ __forceinline__ float read_lane(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-// maximum over the 64 lanes (no NaN among the inputs), uniform
-template <typename T>
-__device__ __forceinline__ T wave_max_dpp(T v) {
-  v = fmax(v, dpp_mov<0xB1>(v));    // quad_perm [1,0,3,2]
-  v = fmax(v, dpp_mov<0x4E>(v));    // quad_perm [2,3,0,1]
-  v = fmax(v, dpp_mov<0x141>(v));   // row_half_mirror
-  v = fmax(v, dpp_mov<0x140>(v));   // row_mirror: every lane holds its 16-lane row's maximum
-  return fmax(fmax(read_lane(v, 0), read_lane(v, 16)), fmax(read_lane(v, 32), read_lane(v, 48)));
-}
-
 // search value of a row: |a| if unused, -1 if used; a NaN wins (and is then
 // reported as a bad pivot)
 template <typename T>

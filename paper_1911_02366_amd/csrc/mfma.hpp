@@ -1,4 +1,5 @@
-// CDNA4 matrix-core helpers: the 16x16x4 MFMA in FP64 and FP32.
+// CDNA4 matrix-core helpers (the 16x16x4 MFMA in FP64 and FP32) and cross-lane
+// reductions.
 //
 // Operand layout within a 64-lane wave (A is 16x4, B is 4x16, D is 16x16),
 // measured on gfx950:
@@ -43,6 +44,52 @@ __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   return v;
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double read_lane(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ __forceinline__ float read_lane(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+// maximum over the 64 lanes (no NaN among the inputs), uniform
+template <typename T>
+__device__ __forceinline__ T wave_max_dpp(T v) {
+  v = fmax(v, dpp_mov<0xB1>(v));    // quad_perm [1,0,3,2]
+  v = fmax(v, dpp_mov<0x4E>(v));    // quad_perm [2,3,0,1]
+  v = fmax(v, dpp_mov<0x141>(v));   // row_half_mirror
+  v = fmax(v, dpp_mov<0x140>(v));   // row_mirror: every lane holds its 16-lane row's maximum
+  return fmax(fmax(read_lane(v, 0), read_lane(v, 16)), fmax(read_lane(v, 32), read_lane(v, 48)));
+}
+
+// maximum over the 64 lanes, uniform
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));
+  const unsigned a = max((unsigned)__builtin_amdgcn_readlane((int)v, 0), (unsigned)__builtin_amdgcn_readlane((int)v, 16));
+  const unsigned b = max((unsigned)__builtin_amdgcn_readlane((int)v, 32), (unsigned)__builtin_amdgcn_readlane((int)v, 48));
+  return max(a, b);
+}
+
+// 1 / d by two Newton steps on the hardware's estimate, for d away from the ends
+// of the range (within an ulp or so of the quotient, a third of its chain)
+__device__ __forceinline__ double fast_reciprocal(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  return fma(fma(-d, r, 1.0), r, r);
 }
 
 }  // namespace scdg

@@ -755,21 +755,22 @@ scdg_status newton_graphs(Plan &p, scdg_dg *dg, const double *q_s, double *q, co
 
 scdg_status dense_solve(Plan &p, const double *bs, double *x) {
   if (!p.dense_factored) {
-    ST_TRY(dalloc(p, &p.s_dense, (size_t)p.n1 * p.n1));
-    ST_TRY(dalloc(p, &p.s_piv, (size_t)p.n1));
-    ST_TRY(dalloc(p, &p.d_dense_info, 1));
-    HIP_TRY(launch_dense_assemble(p, p.s_dense));
-    HIP_TRY(launch_dense_lu(p, p.s_dense, (int32_t)p.n1, p.s_piv, p.d_dense_info));
+    const hipError_t e = launch_dense_lu(p);
+    if (e == hipErrorOutOfMemory) {
+      p.last_error = "out of device memory for the dense LU of S";
+      return SCDG_ERR_NOMEM;
+    }
+    HIP_TRY(e);
     int32_t info = 0;
-    HIP_TRY(hipMemcpy(&info, p.d_dense_info, sizeof(int32_t), hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpyAsync(&info, p.d_dense_info, sizeof(int32_t), hipMemcpyDeviceToHost, p.stream));
+    ST_TRY(sync(p));
     if (info != 0) {
       p.last_error = "zero pivot in the dense LU of S at step " + std::to_string(info);
       return SCDG_ERR_SINGULAR;
     }
     p.dense_factored = true;
   }
-  if (x != bs) HIP_TRY(hipMemcpyAsync(x, bs, sizeof(double) * p.n1, hipMemcpyDeviceToDevice, p.stream));
-  HIP_TRY(launch_dense_solve(p.s_dense, (int32_t)p.n1, p.s_piv, x, p.stream));
+  HIP_TRY(launch_dense_solve(p, bs, x));
   return SCDG_OK;
 }
 
@@ -872,7 +873,8 @@ scdg_status scdg_plan_destroy(scdg_plan *pl) {
   dfree(p.d_gj_voff); dfree(p.d_gj_piv); dfree(p.d_gj_flag); dfree(p.gj_pbuf); dfree(p.gj_rbuf);
   dfree(p.d_gj_desc); dfree(p.d_gj_tiles);
   dfree(p.ainv); dfree(p.ainv_work); dfree(p.xmat); dfree(p.sloc); dfree(p.aib_lo); dfree(p.abi_lo); dfree(p.diag_s);
-  dfree(p.s_dense); dfree(p.s_piv); dfree(p.d_dense_info);
+  dfree(p.s_dense); dfree(p.dl_scale); dfree(p.dl_perm); dfree(p.dl_lbuf); dfree(p.dl_blk); dfree(p.dl_state);
+  dfree(p.dl_x); dfree(p.d_dense_desc); dfree(p.d_dense_info);
   dfree(p.w_z); dfree(p.w_t); dfree(p.w_bs); dfree(p.w_qb); dfree(p.w_r); dfree(p.w_rx); dfree(p.w_dq); dfree(p.w_vec);
   dfree(p.gm_v); dfree(p.gm_w); dfree(p.gm_z); dfree(p.gm_part); dfree(p.gm_h);
   if (p.h_pinned) (void)hipHostFree(p.h_pinned);
