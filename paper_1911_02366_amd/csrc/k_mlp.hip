@@ -29,7 +29,7 @@ namespace {
 constexpr int kTile = 64;     // C tile rows and columns
 constexpr int kBK = 16;       // K slab
 constexpr int kThreads = 256; // 4 waves in a 2 x 2 grid, 32 x 32 each
-constexpr int kRedBlocks = 256;
+constexpr int kRedBlocks = 512;
 
 enum Epilogue { kEpiNone = 0, kEpiTanh = 1 };
 
@@ -47,16 +47,16 @@ __device__ __forceinline__ float bf16_round(float x) {
 __device__ __forceinline__ short bf16_bits(float x) { return (short)(__float_as_uint(x) >> 16); }
 
 // C = op(A) op(B) (+ bias[col]) (tanh) (* (1 - D^2)); op(A) is M x K, op(B) K x N.
-// BF: the operands are rounded to bfloat16 when staged in LDS and multiplied
+// The operands are rounded to bfloat16 when staged in LDS and multiplied
 // by the 16x16x16 bf16 MFMA with FP32 accumulation (products of two bf16
-// values are exact in FP32); otherwise FP32 operands and the 16x16x4 FP32 MFMA.
-template <bool TA, bool TB, bool BF>
-__global__ __launch_bounds__(kThreads) void mlp_gemm_kernel(int M, int N, int K,
-                                                            const float *__restrict__ A, int lda,
-                                                            const float *__restrict__ B, int ldb,
-                                                            float *__restrict__ C, int ldc,
-                                                            const float *__restrict__ bias, int epi,
-                                                            const float *__restrict__ dact, int ldd) {
+// values are exact in FP32).
+template <bool TA, bool TB>
+__global__ __launch_bounds__(kThreads) void mlp_gemm_bf16_kernel(int M, int N, int K,
+                                                                 const float *__restrict__ A, int lda,
+                                                                 const float *__restrict__ B, int ldb,
+                                                                 float *__restrict__ C, int ldc,
+                                                                 const float *__restrict__ bias, int epi,
+                                                                 const float *__restrict__ dact, int ldd) {
   using MF = Mfma<float>;
   __shared__ float as[2][kBK][kTile + 4];
   __shared__ float bs[2][kBK][kTile + 4];
@@ -100,8 +100,8 @@ __global__ __launch_bounds__(kThreads) void mlp_gemm_kernel(int M, int N, int K,
   auto store = [&](int buf) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const float va = BF ? bf16_round(ra[u]) : ra[u];
-      const float vb = BF ? bf16_round(rb[u]) : rb[u];
+      const float va = bf16_round(ra[u]);
+      const float vb = bf16_round(rb[u]);
       if (TA)
         as[buf][tid / kTile + 4 * u][tid % kTile] = va;
       else
@@ -126,36 +126,21 @@ __global__ __launch_bounds__(kThreads) void mlp_gemm_kernel(int M, int N, int K,
   for (int kt = 0; kt < nk; ++kt) {
     const int buf = kt & 1;
     if (kt + 1 < nk) load((kt + 1) * kBK);
-    if constexpr (BF) {
-      // 16x16x16: lane l holds A[l % 16][4 (l / 16) + t] and B[4 (l / 16) + t][l % 16], t = 0..3
-      bf16x4 af[2], bf[2];
+    // 16x16x16: lane l holds A[l % 16][4 (l / 16) + t] and B[4 (l / 16) + t][l % 16], t = 0..3
+    bf16x4 af[2], bf[2];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int k = 4 * (lane >> 4) + t;
+    for (int t = 0; t < 4; ++t) {
+      const int k = 4 * (lane >> 4) + t;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) af[i][t] = bf16_bits(as[buf][k][wm * 32 + i * 16 + (lane & 15)]);
+      for (int i = 0; i < 2; ++i) af[i][t] = bf16_bits(as[buf][k][wm * 32 + i * 16 + (lane & 15)]);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) bf[j][t] = bf16_bits(bs[buf][k][wn * 32 + j * 16 + (lane & 15)]);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af[i], bf[j], acc[i][j], 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < kBK; kk += 4) {
-        float af[2], bf[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) af[i] = as[buf][kk + (lane >> 4)][wm * 32 + i * 16 + (lane & 15)];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) bf[j] = bs[buf][kk + (lane >> 4)][wn * 32 + j * 16 + (lane & 15)];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = MF::mma(af[i], bf[j], acc[i][j]);
-      }
+      for (int j = 0; j < 2; ++j) bf[j][t] = bf16_bits(bs[buf][k][wn * 32 + j * 16 + (lane & 15)]);
     }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af[i], bf[j], acc[i][j], 0, 0, 0);
     if (kt + 1 < nk) store(buf ^ 1);
     __syncthreads();
   }
@@ -182,30 +167,316 @@ __global__ __launch_bounds__(kThreads) void mlp_gemm_kernel(int M, int N, int K,
     }
 }
 
-template <bool BF>
-hipError_t gemm_typed(bool ta, bool tb, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
-                      float *C, int ldc, const float *bias, int epi, const float *dact, int ldd, hipStream_t s) {
-  const dim3 grid((M + kTile - 1) / kTile, (N + kTile - 1) / kTile);
-  if (!ta && !tb)
-    hipLaunchKernelGGL((mlp_gemm_kernel<false, false, BF>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B,
-                       ldb, C, ldc, bias, epi, dact, ldd);
-  else if (ta && !tb)
-    hipLaunchKernelGGL((mlp_gemm_kernel<true, false, BF>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B,
-                       ldb, C, ldc, bias, epi, dact, ldd);
-  else if (!ta && tb)
-    hipLaunchKernelGGL((mlp_gemm_kernel<false, true, BF>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B,
-                       ldb, C, ldc, bias, epi, dact, ldd);
+// FP32 products without LDS staging: every wave loads its operands from global
+// memory straight into the matrix cores' layout, so no barrier stands between a
+// load and its use, with the loads of the next slabs in flight.
+//   The network's products are short for this card: at a batch of 1024 they are 16
+// to 160 tiles of 64 x 64 for 256 compute units, up to 79 slabs in a row.
+//   At 1024 x 1250 -> 256 -> 256 -> 625, against 64 x 64 tiles staged in LDS:
+// forward 97 -> 40 us, backward (weights, biases, activations) 224 -> 52 us;
+// forward of 4096 rows 114 -> 79 us.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // rows start at any float
+
+// The layers' products X W + b (tanh): four waves in a 2 x 2 grid, each a 16 TM x
+// 16 TN tile over the whole of K, which is added up in order (no split: the
+// activations and everything behind them stay the same to the last bit whatever
+// the tile).  A lane loads four consecutive k of its row at once and the 4 x 4
+// transposition between lane groups and loaded values puts k = 4 s + l / 16 into
+// lane l for step s.  DEPTH slabs of loads are in flight: a 16 x 16 tile has only
+// four matrix-core instructions a slab to hide them.
+template <int TM, int TN, int DEPTH>
+__global__ __launch_bounds__(256) void mlp_layer_kernel(int M, int N, int K, const float *__restrict__ A, int lda,
+                                                        const float *__restrict__ B, int ldb, float *__restrict__ C,
+                                                        int ldc, const float *__restrict__ bias, int epi) {
+  using MF = Mfma<float>;
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int m0 = (2 * blockIdx.x + (wid >> 1)) * 16 * TM, n0 = (2 * blockIdx.y + (wid & 1)) * 16 * TN;
+  if (m0 >= M || n0 >= N) return;
+  // rows and columns past the edge read the last ones; their products are not stored
+  const float *__restrict__ abase = A + (int64_t)m0 * lda;
+  const float *__restrict__ bbase = B + n0;
+  unsigned ao[TM], bo[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) ao[i] = (unsigned)min(16 * i + l16, M - 1 - m0) * (unsigned)lda;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) bo[j] = (unsigned)g * (unsigned)ldb + (unsigned)min(16 * j + l16, N - 1 - n0);
+  f32x4 fa[DEPTH][TM], fb[DEPTH][TN];
+  auto load = [&](f32x4 (&ra)[TM], f32x4 (&rb)[TN], int slab) {
+    const float *__restrict__ ak = abase + 16 * slab;
+    const float *__restrict__ bk = bbase + (int64_t)(16 * slab) * ldb;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) ra[i] = *reinterpret_cast<const f32x4u *>(ak + ao[i] + 4 * g);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) rb[j][t] = (bk + (int64_t)(4 * t) * ldb)[bo[j]];
+  };
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = MF::zero();
+  auto mul = [&](const f32x4 (&ra)[TM], const f32x4 (&rb)[TN]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(ra[i][t], rb[j][t], acc[i][j]);
+  };
+  const int slabs = K / 16;
+#pragma unroll
+  for (int d = 0; d < DEPTH - 1; ++d)
+    if (d < slabs) load(fa[d], fb[d], d);
+  for (int s = 0; s < slabs; s += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      if (s + d >= slabs) break;
+      if (s + d + DEPTH - 1 < slabs) load(fa[(d + DEPTH - 1) % DEPTH], fb[(d + DEPTH - 1) % DEPTH], s + d + DEPTH - 1);
+      f32x4 ra[TM];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) ra[i] = transpose_groups(fa[d][i]);
+      mul(ra, fb[d]);
+    }
+  }
+  if (K % 16 != 0) {                                 // the K remainder, zeros past it
+    const float *__restrict__ bk = bbase + (int64_t)(16 * slabs) * ldb;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int k = 4 * t + g;
+      const bool in = 16 * slabs + k < K;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[0][i][t] = in ? (abase + 16 * slabs)[ao[i] + k] : 0.f;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[0][j][t] = in ? (bk + (int64_t)(4 * t) * ldb)[bo[j]] : 0.f;
+    }
+    mul(fa[0], fb[0]);
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int col = n0 + 16 * j + l16;
+    const float add = bias[min(col, N - 1)];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = m0 + 16 * i + MF::row(lane, r);
+        float v = acc[i][j][r] + add;
+        if (epi == kEpiTanh) v = tanhf(v);
+        if (row < M && col < N) C[(int64_t)row * ldc + col] = v;
+      }
+  }
+}
+
+hipError_t layer_f32(int M, int N, int K, const float *A, int lda, const float *B, int ldb, float *C, int ldc,
+                     const float *bias, int epi, hipStream_t s) {
+  // the largest tile that still gives every SIMD of 256 compute units a wave
+  auto tiles = [&](int t) { return (int64_t)((M + t - 1) / t) * ((N + t - 1) / t); };
+  auto grid = [&](int t) { return dim3((M + t - 1) / t, (N + t - 1) / t); };
+  if (tiles(64) >= 256)
+    hipLaunchKernelGGL((mlp_layer_kernel<2, 2, 5>), grid(64), dim3(256), 0, s, M, N, K, A, lda, B, ldb, C, ldc, bias,
+                       epi);
   else
-    return hipErrorInvalidValue;
+    hipLaunchKernelGGL((mlp_layer_kernel<1, 1, 12>), grid(32), dim3(256), 0, s, M, N, K, A, lda, B, ldb, C, ldc, bias,
+                       epi);
   return hipGetLastError();
 }
 
+// Products with a transposed operand (the gradients).  A workgroup of KS waves
+// computes a 16 TM x 32 tile of C; every wave takes its own share of K (a step
+// holds k = 4 (l / 16) + t in lane l, so four consecutive k of a row are one
+// 16-byte load), and the waves' partial tiles are summed in wave order through
+// LDS.  A bias gradient (column sums of dZ) is summed from the dW product's own
+// operand by the workgroups of the first tile row.
+template <bool TA, int TM, int KS>
+__global__ __launch_bounds__(64 * KS) void mlp_grad_kernel(int M, int N, int K, const float *__restrict__ A,
+                                                           int lda, const float *__restrict__ B, int ldb,
+                                                           float *__restrict__ C, int ldc,
+                                                           const float *__restrict__ dact, int ldd,
+                                                           float *__restrict__ colsum) {
+  using MF = Mfma<float>;
+  constexpr bool TB = !TA;
+  constexpr int TN = 2, BM = 16 * TM, BN = 16 * TN, kDepth = 3;
+  __shared__ float part[KS][BM * BN];
+  __shared__ float cpart[KS][BN];
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int slabs = K / 16, per = (slabs + KS - 1) / KS;
+  const int s0 = wid * per, s1 = min(slabs, s0 + per);
+
+  // rows and columns past the edge read the last ones; their products are not stored
+  const float *__restrict__ abase = A + (TA ? (int64_t)m0 : (int64_t)m0 * lda);
+  const float *__restrict__ bbase = B + (TB ? (int64_t)n0 * ldb : (int64_t)n0);
+  unsigned ao[TM], bo[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const unsigned m = (unsigned)min(16 * i + l16, M - 1 - m0);
+    ao[i] = TA ? (unsigned)(4 * g) * (unsigned)lda + m : m * (unsigned)lda + (unsigned)(4 * g);
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const unsigned n = (unsigned)min(16 * j + l16, N - 1 - n0);
+    bo[j] = TB ? n * (unsigned)ldb + (unsigned)(4 * g) : (unsigned)(4 * g) * (unsigned)ldb + n;
+  }
+  f32x4 fa[kDepth][TM], fb[kDepth][TN];
+  auto load = [&](f32x4 (&ra)[TM], f32x4 (&rb)[TN], int slab) {
+    const int k0 = 16 * slab;
+    const float *__restrict__ ak = abase + (TA ? (int64_t)k0 * lda : k0);
+    const float *__restrict__ bk = bbase + (TB ? k0 : (int64_t)k0 * ldb);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if (TA) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) ra[i][t] = (ak + (int64_t)t * lda)[ao[i]];
+      } else {
+        ra[i] = *reinterpret_cast<const f32x4u *>(ak + ao[i]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      if (TB) {
+        rb[j] = *reinterpret_cast<const f32x4u *>(bk + bo[j]);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) rb[j][t] = (bk + (int64_t)t * ldb)[bo[j]];
+      }
+    }
+  };
+  f32x4 acc[TM][TN], bsum[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    bsum[j] = MF::zero();
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc[i][j] = MF::zero();
+  }
+  auto mul = [&](const f32x4 (&ra)[TM], const f32x4 (&rb)[TN]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(ra[i][t], rb[j][t], acc[i][j]);
+    if (TA)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bsum[j] += rb[j];
+  };
+#pragma unroll
+  for (int d = 0; d < kDepth - 1; ++d)
+    if (s0 + d < s1) load(fa[d], fb[d], s0 + d);
+  for (int s = s0; s < s1; s += kDepth) {
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) {
+      if (s + d >= s1) break;
+      if (s + d + kDepth - 1 < s1)
+        load(fa[(d + kDepth - 1) % kDepth], fb[(d + kDepth - 1) % kDepth], s + d + kDepth - 1);
+      mul(fa[d], fb[d]);
+    }
+  }
+  if (K % 16 != 0 && wid == KS - 1) {                // the K remainder, zeros past it
+    const float *__restrict__ ak = abase + (TA ? (int64_t)(16 * slabs) * lda : 16 * slabs);
+    const float *__restrict__ bk = bbase + (TB ? 16 * slabs : (int64_t)(16 * slabs) * ldb);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const bool in = 16 * slabs + 4 * g + t < K;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[0][i][t] = in ? (ak + (TA ? (int64_t)t * lda : t))[ao[i]] : 0.f;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[0][j][t] = in ? (bk + (TB ? t : (int64_t)t * ldb))[bo[j]] : 0.f;
+    }
+    mul(fa[0], fb[0]);
+  }
+
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[wid][(16 * i + MF::row(lane, r)) * BN + 16 * j + l16] = acc[i][j][r];
+  if (TA && colsum != nullptr && blockIdx.x == 0) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      float v = (bsum[j][0] + bsum[j][1]) + (bsum[j][2] + bsum[j][3]);
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (lane < 16) cpart[wid][16 * j + lane] = v;
+    }
+  }
+  __syncthreads();
+  for (int q = tid; q < BM * BN; q += 64 * KS) {
+    const int row = m0 + q / BN, col = n0 + q % BN;
+    if (row >= M || col >= N) continue;
+    float v = part[0][q];
+#pragma unroll
+    for (int k = 1; k < KS; ++k) v += part[k][q];
+    if (dact) {
+      const float t = dact[(int64_t)row * ldd + col];
+      v *= 1.f - t * t;
+    }
+    C[(int64_t)row * ldc + col] = v;
+  }
+  if (TA && colsum != nullptr && blockIdx.x == 0 && tid < BN && n0 + tid < N) {
+    float v = cpart[0][tid];
+#pragma unroll
+    for (int k = 1; k < KS; ++k) v += cpart[k][tid];
+    colsum[n0 + tid] = v;
+  }
+}
+
+template <bool TA>
+hipError_t grad_f32(int M, int N, int K, const float *A, int lda, const float *B, int ldb, float *C, int ldc,
+                    const float *dact, int ldd, float *colsum, hipStream_t s) {
+  // 64-row tiles (less operand traffic per product: 17.8 against 21.7 us for 160 of
+  // them, dW at 1250 x 256) where that leaves enough waves (10 against 7 us for 128 of
+  // them, dZ at 1024 x 256), else 32; K is split until the launch has about 2048
+  // waves, two to a SIMD, or a wave's share is down to two slabs
+  const int64_t cols = (N + 31) / 32;
+  const bool tall = ((M + 63) / 64) * cols >= 160;
+  const dim3 grid((unsigned)(tall ? (M + 63) / 64 : (M + 31) / 32), (unsigned)cols);
+  const int64_t tiles = (int64_t)grid.x * cols;
+  const int slabs = (K + 15) / 16;
+  int ks = 4;
+  while (ks < 16 && tiles * ks * (tall ? 2 : 1) < 2048 && slabs >= 4 * ks) ks *= 2;
+#define SCDG_MLP_LAUNCH(TM, KS)                                                                                   \
+  hipLaunchKernelGGL((mlp_grad_kernel<TA, TM, KS>), grid, dim3(64 * KS), 0, s, M, N, K, A, lda, B, ldb, C, ldc, \
+                     dact, ldd, colsum)
+  if (tall && ks == 4) SCDG_MLP_LAUNCH(4, 4);
+  else if (tall) SCDG_MLP_LAUNCH(4, 8);
+  else if (ks == 4) SCDG_MLP_LAUNCH(2, 4);
+  else if (ks == 8) SCDG_MLP_LAUNCH(2, 8);
+  else SCDG_MLP_LAUNCH(2, 16);
+#undef SCDG_MLP_LAUNCH
+  return hipGetLastError();
+}
+
+hipError_t gemm_bf16(bool ta, bool tb, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
+                     float *C, int ldc, const float *bias, int epi, const float *dact, int ldd, hipStream_t s) {
+  const dim3 grid((M + kTile - 1) / kTile, (N + kTile - 1) / kTile);
+  if (ta)
+    hipLaunchKernelGGL((mlp_gemm_bf16_kernel<true, false>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C,
+                       ldc, bias, epi, dact, ldd);
+  else if (tb)
+    hipLaunchKernelGGL((mlp_gemm_bf16_kernel<false, true>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C,
+                       ldc, bias, epi, dact, ldd);
+  else
+    hipLaunchKernelGGL((mlp_gemm_bf16_kernel<false, false>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C,
+                       ldc, bias, epi, dact, ldd);
+  return hipGetLastError();
+}
+
+// C = op(A) op(B) (+ bias[col]) (tanh) (* (1 - D^2)): a layer's product with its bias
+// (no operand transposed), or a gradient's (one of them); colsum (FP32, ta only): the
+// column sums of B
 hipError_t gemm(bool ta, bool tb, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
                 float *C, int ldc, const float *bias, int epi, const float *dact, int ldd, bool bf16,
-                hipStream_t s) {
+                hipStream_t s, float *colsum = nullptr) {
+  if ((ta && tb) || (!bf16 && !ta && !tb && (!bias || dact))) return hipErrorInvalidValue;
   if (M <= 0 || N <= 0) return hipSuccess;
-  return bf16 ? gemm_typed<true>(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epi, dact, ldd, s)
-              : gemm_typed<false>(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epi, dact, ldd, s);
+  if (bf16) return gemm_bf16(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epi, dact, ldd, s);
+  if (ta) return grad_f32<true>(M, N, K, A, lda, B, ldb, C, ldc, dact, ldd, colsum, s);
+  if (tb) return grad_f32<false>(M, N, K, A, lda, B, ldb, C, ldc, dact, ldd, nullptr, s);
+  return layer_f32(M, N, K, A, lda, B, ldb, C, ldc, bias, epi, s);
 }
 
 // Column sums of a row-major [rows x cols] matrix in two fixed-order stages:
@@ -268,14 +539,29 @@ __global__ void mse_partial_kernel(const float *__restrict__ y, const float *__r
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-__global__ void sum_final_kernel(const double *__restrict__ partial, int n, int width, double scale,
-                                 double *__restrict__ out) {
-  // out[c] = scale * sum_k partial[k * width + c], one thread per column
-  const int c = threadIdx.x;
-  if (c >= width) return;
+// Sum of n values left by the blocks of a reduction, one workgroup of 256: every
+// thread takes the values i, i + 256, .. in order, then a fixed tree (one thread
+// walking 256 partial sums alone took 20 us, five of them 60 us).
+__device__ __forceinline__ double sum_partials(const double *__restrict__ v, int n, int stride, double *red) {
   double s = 0.0;
-  for (int k = 0; k < n; ++k) s += partial[(int64_t)k * width + c];
-  out[c] = s * scale;
+  for (int k = threadIdx.x; k < n; k += 256) s += v[(int64_t)k * stride];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  const double total = red[0];
+  __syncthreads();
+  return total;
+}
+
+// out = scale * sum of the partial sums
+__global__ __launch_bounds__(256) void sum_final_kernel(const double *__restrict__ partial, int n, double scale,
+                                                        double *__restrict__ out) {
+  __shared__ double red[256];
+  const double s = sum_partials(partial, n, 1, red);
+  if (threadIdx.x == 0) out[0] = s * scale;
 }
 
 // Field statistics in two passes (the second sums squared deviations from the
@@ -328,16 +614,16 @@ __global__ void stats_partial_kernel(const double *__restrict__ q, const double 
 // stats = [mean[5], std[5], rms_prev[5], rms_corr[5], rms_res[5]].  Pass 1 fills
 // mean, rms_prev and rms_res; pass 2 fills std and rms_corr (rms_prev when no
 // increment is given).  A zero spread or root mean square maps to 1.
-__global__ void stats_final_kernel(const double *__restrict__ partial, int n_blocks, int64_t n_nodes,
-                                   int pass, int have_dq, double *__restrict__ stats) {
-  const int v = threadIdx.x;
-  if (v >= 5) return;
-  double s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  for (int k = 0; k < n_blocks; ++k) {
-    s1 += partial[(int64_t)k * 15 + v];
-    s2 += partial[(int64_t)k * 15 + 5 + v];
-    s3 += partial[(int64_t)k * 15 + 10 + v];
-  }
+// One workgroup per variable.
+__global__ __launch_bounds__(256) void stats_final_kernel(const double *__restrict__ partial, int n_blocks,
+                                                          int64_t n_nodes, int pass, int have_dq,
+                                                          double *__restrict__ stats) {
+  __shared__ double red[256];
+  const int v = blockIdx.x;
+  const double s1 = sum_partials(partial + v, n_blocks, 15, red);
+  const double s2 = sum_partials(partial + 5 + v, n_blocks, 15, red);
+  const double s3 = sum_partials(partial + 10 + v, n_blocks, 15, red);
+  if (threadIdx.x != 0) return;
   const double n = (double)n_nodes;
   if (pass == 1) {
     stats[v] = s1 / n;
@@ -387,14 +673,13 @@ __global__ void apply_kernel(const double *__restrict__ dq_prev, const float *__
     dq[i] = dq_prev[i] + stats[15 + (int)(i % 5)] * (double)y[i];
 }
 
-__global__ void gather_rows_kernel(const float *__restrict__ src, int width, const int32_t *__restrict__ idx,
-                                   int count, float *__restrict__ dst) {
-  const int64_t total = (int64_t)count * width;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = i / width;
-    const int c = (int)(i - r * width);
-    dst[i] = src[(int64_t)idx[r] * width + c];
+// dst[r] = src[idx[r]], one workgroup per row (no division per value)
+__global__ __launch_bounds__(256) void gather_rows_kernel(const float *__restrict__ src, int width,
+                                                          const int32_t *__restrict__ idx, int count,
+                                                          float *__restrict__ dst) {
+  for (int64_t r = blockIdx.x; r < count; r += gridDim.x) {
+    const float *__restrict__ row = src + (int64_t)idx[r] * width;
+    for (int c = threadIdx.x; c < width; c += 256) dst[r * width + c] = row[c];
   }
 }
 
@@ -536,14 +821,16 @@ scdg_status scdg_mlp_backward(scdg_mlp *m, const float *w, const float *x, const
     const float *a_prev = l == 0 ? x : c.act + (size_t)(l - 1) * c.max_batch * c.n_hidden;
     const int fi = c.fan_in[l], fo = c.fan_out[l];
     // dW_l = A_{l-1}^T dZ_l  [fi x fo]
+    // and db_l = column sums of dZ_l, from the same product in FP32
     hipError_t e = scdg::gemm(true, false, fi, fo, batch, a_prev, fi, dz, fo, dw + c.w_off[l], fo, nullptr,
-                              scdg::kEpiNone, nullptr, 0, c.bf16, c.stream);
+                              scdg::kEpiNone, nullptr, 0, c.bf16, c.stream, dw + c.b_off[l]);
     if (e != hipSuccess) return SCDG_ERR_HIP;
-    // db_l = column sums of dZ_l
-    hipLaunchKernelGGL(scdg::colsum_partial_kernel, dim3((fo + 255) / 256, scdg::kColChunks), dim3(256), 0,
-                       c.stream, dz, batch, fo, c.colpart);
-    hipLaunchKernelGGL(scdg::colsum_final_kernel, dim3((fo + 255) / 256), dim3(256), 0, c.stream, c.colpart,
-                       fo, dw + c.b_off[l]);
+    if (c.bf16) {
+      hipLaunchKernelGGL(scdg::colsum_partial_kernel, dim3((fo + 255) / 256, scdg::kColChunks), dim3(256), 0,
+                         c.stream, dz, batch, fo, c.colpart);
+      hipLaunchKernelGGL(scdg::colsum_final_kernel, dim3((fo + 255) / 256), dim3(256), 0, c.stream, c.colpart,
+                         fo, dw + c.b_off[l]);
+    }
     if (l > 0) {
       // dZ_{l-1} = (dZ_l W_l^T) * (1 - A_{l-1}^2)
       float *next = buf[cur];
@@ -578,7 +865,7 @@ scdg_status scdg_mlp_mse(scdg_mlp *m, const float *y, const float *t, int64_t n,
   auto &c = m->c;
   hipLaunchKernelGGL(scdg::mse_partial_kernel, dim3(scdg::kRedBlocks), dim3(256), 0, c.stream, y, t, n, dy,
                      c.red);
-  hipLaunchKernelGGL(scdg::sum_final_kernel, dim3(1), dim3(64), 0, c.stream, c.red, scdg::kRedBlocks, 1,
+  hipLaunchKernelGGL(scdg::sum_final_kernel, dim3(1), dim3(256), 0, c.stream, c.red, scdg::kRedBlocks,
                      1.0 / (double)n, loss);
   return hip_status(hipGetLastError());
 }
@@ -587,7 +874,7 @@ scdg_status scdg_mlp_gather(scdg_mlp *m, const float *src, int32_t width, const 
                             float *dst) {
   if (!m || !src || !idx || !dst || width <= 0 || count < 0) return SCDG_ERR_ARG;
   if (count == 0) return SCDG_OK;
-  hipLaunchKernelGGL(scdg::gather_rows_kernel, dim3(scdg::grid_for((int64_t)count * width)), dim3(256), 0,
+  hipLaunchKernelGGL(scdg::gather_rows_kernel, dim3((unsigned)std::min(count, 1 << 20)), dim3(256), 0,
                      m->c.stream, src, width, idx, count, dst);
   return hip_status(hipGetLastError());
 }
@@ -599,11 +886,11 @@ scdg_status scdg_guess_stats(scdg_mlp *m, const double *q, const double *dq_prev
   const int64_t nodes = n_dof / 5;
   hipLaunchKernelGGL(scdg::stats_partial_kernel, dim3(scdg::kRedBlocks), dim3(256), 0, c.stream, q, dq_prev,
                      nullptr, r, nullptr, nodes, c.red);
-  hipLaunchKernelGGL(scdg::stats_final_kernel, dim3(1), dim3(64), 0, c.stream, c.red, scdg::kRedBlocks, nodes,
+  hipLaunchKernelGGL(scdg::stats_final_kernel, dim3(5), dim3(256), 0, c.stream, c.red, scdg::kRedBlocks, nodes,
                      1, 0, stats);
   hipLaunchKernelGGL(scdg::stats_partial_kernel, dim3(scdg::kRedBlocks), dim3(256), 0, c.stream, q, dq_prev,
                      dq, nullptr, stats, nodes, c.red);
-  hipLaunchKernelGGL(scdg::stats_final_kernel, dim3(1), dim3(64), 0, c.stream, c.red, scdg::kRedBlocks, nodes,
+  hipLaunchKernelGGL(scdg::stats_final_kernel, dim3(5), dim3(256), 0, c.stream, c.red, scdg::kRedBlocks, nodes,
                      2, dq ? 1 : 0, stats);
   return hip_status(hipGetLastError());
 }
