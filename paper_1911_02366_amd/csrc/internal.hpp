@@ -15,6 +15,7 @@ constexpr int kNvar = 5;
 constexpr int kMaxOrder = 7;
 constexpr int kGjOuter = 128;        // outer panel width of the blocked Gauss-Jordan inverse
 constexpr int kDensePanel = 64;       // panel width of the dense LU of S
+constexpr int kKrylovBlocks = 256;    // workgroups (partial sums per value) of the Gram-Schmidt launches
 constexpr int kGjAutoBlocked = 320;  // automatic choice: blocked form above this n_i
 
 // One GEMM problem of a batched launch: C = alpha A B + beta C, row-major with
@@ -71,15 +72,22 @@ struct KrylovKey {
   bool fp32 = false;
   const void *sloc = nullptr, *bb_val = nullptr, *gm_v = nullptr;
   // the matrix-free forms' operands: block-sparse lists, work vector, and the
-  // caller's A_ib / A_bi (their addresses can change with every assemble)
-  const void *sp[7] = {};
+  // caller's A_ib / A_bi (their addresses can change with every assemble); the
+  // cycle's own state
+  const void *sp[8] = {};
   bool operator==(const KrylovKey &o) const {
-    for (int i = 0; i < 7; ++i)
+    for (int i = 0; i < 8; ++i)
       if (sp[i] != o.sp[i]) return false;
     return m == o.m && pmode == o.pmode && smode == o.smode && sp_gen == o.sp_gen && fp32 == o.fp32 &&
            sloc == o.sloc &&
            bb_val == o.bb_val && gm_v == o.gm_v;
   }
+};
+
+// Device state of a GMRES cycle (see k_vec.hip)
+struct KrylovState {
+  double *H, *cs, *sn, *g, *dev;
+  int32_t *st;
 };
 
 // A block-sparse element operator (rows of 5x5 blocks): the nonzero blocks of
@@ -242,17 +250,20 @@ struct Plan {
   double *gm_w = nullptr;     // [n1]
   double *gm_z = nullptr;     // [n1]
   double *gm_part = nullptr;  // reduction partials
+  double *kr_part = nullptr;  // partial sums of a GMRES iteration: 2 x 64 values, norm
   double *gm_h = nullptr;     // [m+2] device h column
   double *h_pinned = nullptr; // host pinned staging
   int32_t gm_m = 0;
 
   // device-resident GMRES cycles (krylov_mode 1) and their graph (mode 2)
-  int krylov_mode = 0;            // 0 host Givens, 1 device, 2 device + graph replay
+  int krylov_mode = 0;            // 0 stopped by the host, 1 whole cycles, 2 graph replay
   const int32_t *halt = nullptr;  // set while enqueueing Arnoldi steps: kernels return when *halt
   bool capturing = false;
   double *kr_H = nullptr, *kr_cs = nullptr, *kr_sn = nullptr, *kr_g = nullptr, *kr_dev = nullptr;
   int32_t *kr_st = nullptr;
   int kr_m = 0;
+  int32_t *kr_host = nullptr;     // pinned [64][2]: flag and iteration count per iteration
+  hipEvent_t kr_ev[2] = {};
   hipStream_t cap_stream = nullptr;   // plan-owned stream for graph capture
   hipGraph_t kr_graph = nullptr;
   hipGraphExec_t kr_exec = nullptr;
@@ -265,7 +276,6 @@ struct Plan {
   hipGraph_t nw_graph[3] = {};        // 0: right-hand side and GMRES set-up, 1: one restart
   hipGraphExec_t nw_exec[3] = {};     //    cycle, 2: back-substitution, update and residual
   NewtonKey nw_key{};
-  int32_t red_blocks = 0;
 
   // phase timing (events recorded asynchronously, summed on query)
   bool timing = false;
@@ -321,8 +331,6 @@ hipError_t launch_bsr5_rows(int64_t n_rows, const int64_t *rowptr, const int32_t
                             bool fp32, const double *x, const int64_t *ybase, double *y, hipStream_t s,
                             const int32_t *halt);
 hipError_t launch_precond_setup(const Plan &p, const void *t, bool fp32);
-// y = a M^-1 x with M = I (mode 0), diag(S) (1) or the 5x5 node blocks of S (2)
-hipError_t launch_precond_apply(const Plan &p, int mode, const double *x, double *y, double a);
 
 hipError_t launch_gather(const double *src, const int32_t *map, double *dst, int64_t n, hipStream_t s);
 // dst[b * 25 + k] = src[idx[b] * 25 + k]  (5x5 blocks)
@@ -339,28 +347,25 @@ hipError_t launch_fill(double *y, int64_t n, double v, hipStream_t s, const int3
 hipError_t launch_scatter_axpby(int64_t n, double a, const double *x, double b, const double *yin,
                                 const int32_t *map, double *dst, hipStream_t s);
 
-// multi-dot: out[k] = sum_i V[k*ld + i] w[i], k < nv (deterministic two-stage)
-hipError_t launch_multidot(const double *v, int64_t ld, int32_t nv, const double *w, int64_t n,
-                           double *partials, int32_t nblocks, double *out, hipStream_t s,
-                           const int32_t *halt = nullptr);
-// w -= sum_k V[k*ld+i] h[k]
-hipError_t launch_multi_axpy(const double *v, int64_t ld, int32_t nv, const double *h, double *w,
-                             int64_t n, hipStream_t s,
-                             const int32_t *nv_dev = nullptr, const int32_t *halt = nullptr);
-// y = x * dinv (elementwise); dinv may be null (copy)
-hipError_t launch_diag_scale(const double *x, const double *dinv, double *y, int64_t n, double a,
-                             hipStream_t s,
-                             const double *a_dev = nullptr, const int32_t *halt = nullptr);
+// out = ||x||^2 (deterministic two-stage sum; part: kKrylovBlocks partial sums), and the
+// second stage alone (out[1] = st[1] when st is given)
+hipError_t launch_norm2(const double *x, int64_t n, double *part, double *out, hipStream_t s);
+hipError_t launch_sum_parts(const double *part, const int32_t *st, double *out, hipStream_t s);
 hipError_t launch_reciprocal(double *x, int64_t n, hipStream_t s);
-hipError_t launch_krylov_start(double beta, double target, int limit, double *g, int32_t *st, double *dev,
-                               hipStream_t s);
-hipError_t launch_krylov_givens(int j, int m, const double *hc, double *H, double *cs, double *sn, double *g,
-                                int32_t *st, double *dev, hipStream_t s);
-hipError_t launch_krylov_solve(int m, const double *H, const double *g, const int32_t *st, double *yneg,
-                               hipStream_t s, const int32_t *halt = nullptr);
+hipError_t launch_krylov_gram_schmidt(const double *v, int64_t ld, int nv, double *w, int64_t n, double *part,
+                                      double *h1, double *h2, double *norm_part, hipStream_t s,
+                                      const int32_t *halt);
+hipError_t launch_krylov_first(const Plan &p, const double *r, const double *a_dev, double beta, double target,
+                               int limit, int mode, const KrylovState &ks, const int32_t *halt);
+hipError_t launch_krylov_next(const Plan &p, int j, int m, int mode, const double *norm_part, const double *h1,
+                              const double *h2, const KrylovState &ks, int32_t *host_st);
+hipError_t launch_krylov_update(const Plan &p, int m, int mode, const KrylovState &ks, double *y, double *x,
+                                const int32_t *halt);
+hipError_t launch_krylov_residual(const double *b, double *r, int64_t n, double *part, hipStream_t s,
+                                  const int32_t *halt);
 hipError_t launch_newton_gmres_setup(const double *stat, double eta_c, double lin_tol, double eta_max, int m,
                                      double *g, int32_t *st, double *dev, hipStream_t s);
-hipError_t launch_newton_gmres_restart(const double *stat, int m, double *g, int32_t *st, double *dev,
+hipError_t launch_newton_gmres_restart(const double *part, int m, double *g, int32_t *st, double *dev,
                                        hipStream_t s);
 
 // device residual R(Q) of a scdg_dg object (k_dgsem.hip), enqueued on stream s

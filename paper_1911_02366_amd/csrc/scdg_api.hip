@@ -185,7 +185,7 @@ scdg_status sync(Plan &p) {
 
 // ||x||_2^2 of a device vector, result on host (synchronizes)
 scdg_status norm2sq(Plan &p, const double *x, int64_t n, double *out) {
-  HIP_TRY(launch_multidot(x, 0, 1, x, n, p.gm_part, p.red_blocks, p.gm_h, p.stream));
+  HIP_TRY(launch_norm2(x, n, p.gm_part, p.gm_h, p.stream));
   HIP_TRY(hipMemcpyAsync(p.h_pinned, p.gm_h, sizeof(double), hipMemcpyDeviceToHost, p.stream));
   ST_TRY(sync(p));
   *out = p.h_pinned[0];
@@ -356,22 +356,18 @@ scdg_status ensure_gmres(Plan &p, int m) {
   return SCDG_OK;
 }
 
-// One Arnoldi step j of the device-resident cycle: every kernel first reads the
-// halt flag (p.halt) and returns at once after convergence, so the fixed
-// sequence of m steps can be replayed from a graph.
-scdg_status krylov_step(Plan &p, int j, int m, int pmode) {
-  const int64_t n = p.n1;
-  double *vj = p.gm_v + (int64_t)j * n;
-  double *w = p.gm_w;
-  HIP_TRY(launch_precond_apply(p, pmode, vj, p.gm_z, 1.0));
-  ST_TRY(schur_apply_impl(p, p.gm_z, w));
-  HIP_TRY(launch_multidot(p.gm_v, n, j + 1, w, n, p.gm_part, p.red_blocks, p.gm_h, p.stream, p.halt));
-  HIP_TRY(launch_multi_axpy(p.gm_v, n, j + 1, p.gm_h, w, n, p.stream, nullptr, p.halt));
-  HIP_TRY(launch_multidot(p.gm_v, n, j + 1, w, n, p.gm_part, p.red_blocks, p.gm_h + (m + 1), p.stream, p.halt));
-  HIP_TRY(launch_multi_axpy(p.gm_v, n, j + 1, p.gm_h + (m + 1), w, n, p.stream, nullptr, p.halt));
-  HIP_TRY(launch_multidot(w, 0, 1, w, n, p.gm_part, p.red_blocks, p.gm_h + 2 * (m + 1), p.stream, p.halt));
-  HIP_TRY(launch_krylov_givens(j, m, p.gm_h, p.kr_H, p.kr_cs, p.kr_sn, p.kr_g, p.kr_st, p.kr_dev, p.stream));
-  HIP_TRY(launch_diag_scale(w, nullptr, p.gm_v + (int64_t)(j + 1) * n, n, 1.0, p.stream, p.kr_dev, p.halt));
+KrylovState krylov_state(const Plan &p) { return KrylovState{p.kr_H, p.kr_cs, p.kr_sn, p.kr_g, p.kr_dev, p.kr_st}; }
+double *krylov_norm_part(const Plan &p) { return p.kr_part + 2 * 64 * kKrylovBlocks; }
+
+// One Arnoldi step j of a cycle: every kernel first reads the halt flag (p.halt)
+// and returns at once after convergence, so steps can be enqueued ahead of the
+// result and a fixed sequence of m steps be replayed from a graph.  gm_z holds the
+// preconditioned basis vector j on entry and j + 1 on return.
+scdg_status krylov_step(Plan &p, int j, int m, int pmode, int32_t *host_st = nullptr) {
+  ST_TRY(schur_apply_impl(p, p.gm_z, p.gm_w));
+  HIP_TRY(launch_krylov_gram_schmidt(p.gm_v, p.n1, j + 1, p.gm_w, p.n1, p.kr_part, p.gm_h, p.gm_h + (m + 1),
+                                     krylov_norm_part(p), p.stream, p.halt));
+  HIP_TRY(launch_krylov_next(p, j, m, pmode, krylov_norm_part(p), p.gm_h, p.gm_h + (m + 1), krylov_state(p), host_st));
   return SCDG_OK;
 }
 
@@ -392,8 +388,8 @@ scdg_status krylov_graph(Plan &p, int m, int pmode) {
   key.bb_val = p.bb_val;
   key.gm_v = p.gm_v;
   key.smode = p.schur_mode;
-  const void *sp[7] = {p.sp_ib.val, p.sp_ib.d_rowptr, p.sp_bi.val, p.sp_bi.d_rowptr, p.w_z2, p.aib, p.abi};
-  for (int i = 0; i < 7; ++i) key.sp[i] = sp[i];
+  const void *sp[8] = {p.sp_ib.val, p.sp_ib.d_rowptr, p.sp_bi.val, p.sp_bi.d_rowptr, p.w_z2, p.aib, p.abi, p.kr_H};
+  for (int i = 0; i < 8; ++i) key.sp[i] = sp[i];
   key.sp_gen = p.sp_gen;
   if (p.kr_exec && p.kr_key == key) return SCDG_OK;
   drop_krylov_graph(p);
@@ -427,6 +423,11 @@ scdg_status krylov_graph(Plan &p, int m, int pmode) {
 }
 
 scdg_status ensure_krylov_state(Plan &p, int m) {
+  if (!p.kr_part) ST_TRY(dalloc(p, &p.kr_part, (size_t)(2 * 64 + 1) * kKrylovBlocks));
+  if (!p.kr_host)
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&p.kr_host), sizeof(int32_t) * 2 * 64));
+  for (hipEvent_t &e : p.kr_ev)
+    if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   if (p.kr_H && p.kr_m >= m) return SCDG_OK;
   dfree(p.kr_H); dfree(p.kr_cs); dfree(p.kr_sn); dfree(p.kr_g); dfree(p.kr_st); dfree(p.kr_dev);
   ST_TRY(dalloc(p, &p.kr_H, (size_t)(m + 1) * m));
@@ -439,16 +440,39 @@ scdg_status ensure_krylov_state(Plan &p, int m) {
   return SCDG_OK;
 }
 
+// Steps of a cycle enqueued one ahead of the result: the host waits for step j - 1
+// once step j is enqueued, so the device never waits for the host; a step past the
+// end of the cycle returns at once and is not timed.
+scdg_status krylov_steps_watched(Plan &p, int limit, int m, int pmode) {
+  for (int j = 0; j < limit; ++j) {
+    const size_t timed = p.ev_used.size();
+    p.halt = p.kr_st;
+    const scdg_status st = krylov_step(p, j, m, pmode, p.kr_host + 2 * j);
+    p.halt = nullptr;
+    if (st != SCDG_OK) return st;
+    HIP_TRY(hipEventRecord(p.kr_ev[j & 1], p.stream));
+    if (j == 0) continue;
+    HIP_TRY(hipEventSynchronize(p.kr_ev[(j - 1) & 1]));
+    if (p.kr_host[2 * (j - 1)]) {
+      for (; p.ev_used.size() > timed; p.ev_used.pop_back()) p.ev_pool.push_back(p.ev_used.back().second);
+      break;
+    }
+  }
+  return SCDG_OK;
+}
+
 // Restart cycles with the Hessenberg column, the Givens rotations and the stopping
-// test on the device; the host waits once per cycle (true residual).  r holds
-// bs - S x on entry, beta its norm.
-scdg_status gmres_device_cycles(Plan &p, const double *bs, double *x, double *r, double bnorm, double beta,
-                                const scdg_solve_opts &o, scdg_solve_info &info) {
+// test on the device; the host looks at the stopping flag of every step (mode 0) or
+// waits once per cycle (modes 1, 2), and takes the true residual after each.  r
+// holds bs - S x on entry, beta its norm.
+scdg_status gmres_cycles(Plan &p, const double *bs, double *x, double *r, double bnorm, double beta,
+                         const scdg_solve_opts &o, scdg_solve_info &info) {
   const int64_t n = p.n1;
   const int m = o.restart;
   const int pmode = o.precond;
   const double target = o.tol * bnorm;
   ST_TRY(ensure_krylov_state(p, m));
+  const KrylovState ks = krylov_state(p);
   const bool use_graph = p.krylov_mode == 2;
   if (use_graph) {
     p.halt = p.kr_st;
@@ -464,10 +488,11 @@ scdg_status gmres_device_cycles(Plan &p, const double *bs, double *x, double *r,
     }
     ++info.restarts;
     const int limit = std::min(m, o.max_iters - it);
-    HIP_TRY(launch_diag_scale(r, nullptr, p.gm_v, n, 1.0 / beta, p.stream));
-    HIP_TRY(launch_krylov_start(beta, target, limit, p.kr_g, p.kr_st, p.kr_dev, p.stream));
+    HIP_TRY(launch_krylov_first(p, r, nullptr, beta, target, limit, pmode, ks, nullptr));
     if (use_graph) {
       HIP_TRY(hipGraphLaunch(p.kr_exec, p.stream));
+    } else if (p.krylov_mode == 0) {
+      ST_TRY(krylov_steps_watched(p, limit, m, pmode));
     } else {
       p.halt = p.kr_st;
       scdg_status st = SCDG_OK;
@@ -475,24 +500,18 @@ scdg_status gmres_device_cycles(Plan &p, const double *bs, double *x, double *r,
       p.halt = nullptr;
       if (st != SCDG_OK) return st;
     }
-    // x += Dinv (V y)
-    HIP_TRY(launch_krylov_solve(m, p.kr_H, p.kr_g, p.kr_st, p.gm_h, p.stream));
-    HIP_TRY(hipMemsetAsync(p.gm_z, 0, sizeof(double) * n, p.stream));
-    HIP_TRY(launch_multi_axpy(p.gm_v, n, m, p.gm_h, p.gm_z, n, p.stream, p.kr_st + 1, nullptr));
-    HIP_TRY(launch_precond_apply(p, pmode, p.gm_z, p.gm_w, 1.0));
-    HIP_TRY(launch_axpby(n, 1.0, p.gm_w, 1.0, x, p.stream));
-    HIP_TRY(hipMemcpyAsync(p.h_pinned + 8, p.kr_st, sizeof(int32_t) * 2, hipMemcpyDeviceToHost, p.stream));
-    // true residual
+    // x += Dinv (V y), the true residual and its norm
+    HIP_TRY(launch_krylov_update(p, m, pmode, ks, p.gm_h, x, nullptr));
     ST_TRY(schur_apply_impl(p, x, r));
-    HIP_TRY(launch_axpby(n, 1.0, bs, -1.0, r, p.stream));
-    double beta2;
-    ST_TRY(norm2sq(p, r, n, &beta2));
-    int32_t done[2];
-    std::memcpy(done, p.h_pinned + 8, sizeof(done));
-    it += done[1];
-    beta = std::sqrt(beta2);
+    HIP_TRY(launch_krylov_residual(bs, r, n, krylov_norm_part(p), p.stream, nullptr));
+    HIP_TRY(launch_sum_parts(krylov_norm_part(p), p.kr_st, p.gm_h, p.stream));
+    HIP_TRY(hipMemcpyAsync(p.h_pinned, p.gm_h, sizeof(double) * 2, hipMemcpyDeviceToHost, p.stream));
+    ST_TRY(sync(p));
+    const int done = (int)p.h_pinned[1];
+    it += done;
+    beta = std::sqrt(p.h_pinned[0]);
     info.rel_res_S = beta / bnorm;
-    if (done[1] == 0) break;   // no progress possible (breakdown at the first step)
+    if (done == 0) break;   // no progress possible (breakdown at the first step)
   }
   info.iters += it;
   if (beta > target) {
@@ -507,7 +526,6 @@ scdg_status gmres(Plan &p, const double *bs, double *x, const double *x0, const 
   const int64_t n = p.n1;
   const int m = o.restart;
   ST_TRY(ensure_gmres(p, m));
-  const int pmode = o.precond;  // 0 none, 1 point Jacobi, 2 5x5 node-block Jacobi
   double bnorm2;
   ST_TRY(norm2sq(p, bs, n, &bnorm2));
   if (!std::isfinite(bnorm2)) {
@@ -521,102 +539,26 @@ scdg_status gmres(Plan &p, const double *bs, double *x, const double *x0, const 
     return SCDG_OK;
   }
   double *r = p.gm_w;
+  double beta = bnorm;
   if (x0) {
     if (x0 != x) HIP_TRY(hipMemcpyAsync(x, x0, sizeof(double) * n, hipMemcpyDeviceToDevice, p.stream));
     ST_TRY(schur_apply_impl(p, x, r));
     HIP_TRY(launch_axpby(n, 1.0, bs, -1.0, r, p.stream));  // r = bs - S x
-  } else {
-    HIP_TRY(hipMemsetAsync(x, 0, sizeof(double) * n, p.stream));
-    HIP_TRY(hipMemcpyAsync(r, bs, sizeof(double) * n, hipMemcpyDeviceToDevice, p.stream));
-  }
-  double beta2;
-  ST_TRY(norm2sq(p, r, n, &beta2));
-  double beta = std::sqrt(beta2);
-  if (info.rel_res_guess < 0) info.rel_res_guess = x0 ? beta / bnorm : 1.0;
-  if (x0 && !(beta <= bnorm)) {
-    // the guess is worse than none (or not finite): start from zero instead
-    info.guess_rejected = 1;
-    HIP_TRY(hipMemsetAsync(x, 0, sizeof(double) * n, p.stream));
-    HIP_TRY(hipMemcpyAsync(r, bs, sizeof(double) * n, hipMemcpyDeviceToDevice, p.stream));
-    beta = bnorm;
-  }
-  if (p.krylov_mode != 0) return gmres_device_cycles(p, bs, x, r, bnorm, beta, o, info);
-  std::vector<double> h((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m);
-  int it = 0;
-  const double target = o.tol * bnorm;
-  while (it < o.max_iters && beta > target) {
-    if (!std::isfinite(beta)) {
-      p.last_error = "non-finite GMRES residual";
-      return SCDG_ERR_NONFINITE;
-    }
-    ++info.restarts;
-    HIP_TRY(launch_diag_scale(r, nullptr, p.gm_v, n, 1.0 / beta, p.stream));
-    std::fill(h.begin(), h.end(), 0.0);
-    std::fill(g.begin(), g.end(), 0.0);
-    g[0] = beta;
-    int jused = 0;
-    for (int j = 0; j < m && it < o.max_iters; ++j) {
-      double *vj = p.gm_v + (int64_t)j * n;
-      double *w = p.gm_w;
-      HIP_TRY(launch_precond_apply(p, pmode, vj, p.gm_z, 1.0));
-      ST_TRY(schur_apply_impl(p, p.gm_z, w));
-      // classical Gram-Schmidt, twice (FP64)
-      HIP_TRY(launch_multidot(p.gm_v, n, j + 1, w, n, p.gm_part, p.red_blocks, p.gm_h, p.stream));
-      HIP_TRY(launch_multi_axpy(p.gm_v, n, j + 1, p.gm_h, w, n, p.stream));
-      HIP_TRY(launch_multidot(p.gm_v, n, j + 1, w, n, p.gm_part, p.red_blocks, p.gm_h + (m + 1),
-                              p.stream));
-      HIP_TRY(launch_multi_axpy(p.gm_v, n, j + 1, p.gm_h + (m + 1), w, n, p.stream));
-      HIP_TRY(launch_multidot(w, 0, 1, w, n, p.gm_part, p.red_blocks, p.gm_h + 2 * (m + 1), p.stream));
-      HIP_TRY(hipMemcpyAsync(p.h_pinned, p.gm_h, sizeof(double) * 3 * (m + 1), hipMemcpyDeviceToHost,
-                             p.stream));
-      ST_TRY(sync(p));
-      for (int i = 0; i <= j; ++i) h[(size_t)i * m + j] = p.h_pinned[i] + p.h_pinned[(m + 1) + i];
-      const double hn = std::sqrt(std::max(0.0, p.h_pinned[2 * (m + 1)]));
-      h[(size_t)(j + 1) * m + j] = hn;
-      if (hn > 0.0)
-        HIP_TRY(launch_diag_scale(w, nullptr, p.gm_v + (int64_t)(j + 1) * n, n, 1.0 / hn, p.stream));
-      for (int i = 0; i < j; ++i) {
-        const double t = cs[i] * h[(size_t)i * m + j] + sn[i] * h[(size_t)(i + 1) * m + j];
-        h[(size_t)(i + 1) * m + j] = -sn[i] * h[(size_t)i * m + j] + cs[i] * h[(size_t)(i + 1) * m + j];
-        h[(size_t)i * m + j] = t;
-      }
-      const double den = std::hypot(h[(size_t)j * m + j], hn);
-      cs[j] = den > 0 ? h[(size_t)j * m + j] / den : 1.0;
-      sn[j] = den > 0 ? hn / den : 0.0;
-      h[(size_t)j * m + j] = den;
-      h[(size_t)(j + 1) * m + j] = 0.0;
-      g[j + 1] = -sn[j] * g[j];
-      g[j] = cs[j] * g[j];
-      ++it;
-      jused = j + 1;
-      info.rel_res_S = std::fabs(g[j + 1]) / bnorm;
-      if (std::fabs(g[j + 1]) <= target || hn == 0.0) break;
-    }
-    for (int i = jused - 1; i >= 0; --i) {
-      double v = g[i];
-      for (int q = i + 1; q < jused; ++q) v -= h[(size_t)i * m + q] * y[q];
-      y[i] = v / h[(size_t)i * m + i];
-    }
-    // x += Dinv (V y): accumulate V y into z with negated coefficients
-    for (int i = 0; i < jused; ++i) p.h_pinned[i] = -y[i];
-    HIP_TRY(hipMemcpyAsync(p.gm_h, p.h_pinned, sizeof(double) * jused, hipMemcpyHostToDevice, p.stream));
-    HIP_TRY(hipMemsetAsync(p.gm_z, 0, sizeof(double) * n, p.stream));
-    HIP_TRY(launch_multi_axpy(p.gm_v, n, jused, p.gm_h, p.gm_z, n, p.stream));
-    HIP_TRY(launch_precond_apply(p, pmode, p.gm_z, p.gm_w, 1.0));
-    HIP_TRY(launch_axpby(n, 1.0, p.gm_w, 1.0, x, p.stream));
-    // true residual
-    ST_TRY(schur_apply_impl(p, x, r));
-    HIP_TRY(launch_axpby(n, 1.0, bs, -1.0, r, p.stream));
+    double beta2;
     ST_TRY(norm2sq(p, r, n, &beta2));
     beta = std::sqrt(beta2);
-    info.rel_res_S = beta / bnorm;
   }
-  info.iters += it;
-  if (beta > target) {
-    p.last_error = "GMRES did not reach the tolerance";
-    return SCDG_ERR_NOCONV;
+  if (info.rel_res_guess < 0) info.rel_res_guess = x0 ? beta / bnorm : 1.0;
+  if (x0 && !(beta <= bnorm)) {
+    info.guess_rejected = 1;   // the guess is worse than none (or not finite): start from zero instead
+    x0 = nullptr;
+    beta = bnorm;
   }
-  return SCDG_OK;
+  if (!x0) {
+    HIP_TRY(hipMemsetAsync(x, 0, sizeof(double) * n, p.stream));
+    HIP_TRY(hipMemcpyAsync(r, bs, sizeof(double) * n, hipMemcpyDeviceToDevice, p.stream));
+  }
+  return gmres_cycles(p, bs, x, r, bnorm, beta, o, info);
 }
 
 // ---- one Newton iteration of the implicit step, captured as a graph ----
@@ -668,11 +610,11 @@ scdg_status newton_piece_setup(Plan &p, const NewtonSetup &ns) {
   const int64_t n = p.n1;
   p.halt = nullptr;
   ST_TRY(condense_rhs_impl(p, p.nw_r, p.w_bs));
-  HIP_TRY(launch_multidot(p.w_bs, 0, 1, p.w_bs, n, p.gm_part, p.red_blocks, p.nw_stat + 1, p.stream));
+  HIP_TRY(launch_norm2(p.w_bs, n, p.gm_part, p.nw_stat + 1, p.stream));
   HIP_TRY(launch_fill(p.w_qb, n, 0.0, p.stream));
   HIP_TRY(launch_newton_gmres_setup(p.nw_stat, ns.eta_c, ns.lin_tol, ns.eta_max, ns.m, p.kr_g, p.kr_st,
                                     p.kr_dev, p.stream));
-  HIP_TRY(launch_diag_scale(p.w_bs, nullptr, p.gm_v, n, 1.0, p.stream, p.kr_dev, p.kr_st + 3));
+  HIP_TRY(launch_krylov_first(p, p.w_bs, p.kr_dev, 0.0, 0.0, 0, ns.pmode, krylov_state(p), p.kr_st + 3));
   return SCDG_OK;
 }
 
@@ -690,18 +632,13 @@ scdg_status newton_piece_cycle(Plan &p, const NewtonSetup &ns) {
   for (int j = 0; j < m && s1 == SCDG_OK; ++j) s1 = krylov_step(p, j, m, ns.pmode);
   p.halt = done;
   if (s1 == SCDG_OK) {
-    HIP_TRY(launch_krylov_solve(m, p.kr_H, p.kr_g, st, p.gm_h, p.stream, done));
-    HIP_TRY(launch_fill(p.gm_z, n, 0.0, p.stream, done));
-    HIP_TRY(launch_multi_axpy(p.gm_v, n, m, p.gm_h, p.gm_z, n, p.stream, st + 1, done));
-    HIP_TRY(launch_precond_apply(p, ns.pmode, p.gm_z, rg, 1.0));
-    HIP_TRY(launch_axpby(n, 1.0, rg, 1.0, p.w_qb, p.stream, done));
+    HIP_TRY(launch_krylov_update(p, m, ns.pmode, krylov_state(p), p.gm_h, p.w_qb, done));
     s1 = schur_apply_impl(p, p.w_qb, rg);
   }
   if (s1 == SCDG_OK) {
-    HIP_TRY(launch_axpby(n, 1.0, p.w_bs, -1.0, rg, p.stream, done));
-    HIP_TRY(launch_multidot(rg, 0, 1, rg, n, p.gm_part, p.red_blocks, p.nw_stat + 3, p.stream, done));
-    HIP_TRY(launch_newton_gmres_restart(p.nw_stat, m, p.kr_g, st, p.kr_dev, p.stream));
-    HIP_TRY(launch_diag_scale(rg, nullptr, p.gm_v, n, 1.0, p.stream, p.kr_dev, done));
+    HIP_TRY(launch_krylov_residual(p.w_bs, rg, n, krylov_norm_part(p), p.stream, done));
+    HIP_TRY(launch_newton_gmres_restart(krylov_norm_part(p), m, p.kr_g, st, p.kr_dev, p.stream));
+    HIP_TRY(launch_krylov_first(p, rg, p.kr_dev, 0.0, 0.0, 0, ns.pmode, krylov_state(p), done));
   }
   p.halt = nullptr;
   return s1;
@@ -713,7 +650,7 @@ scdg_status newton_piece_update(Plan &p, scdg_dg *dg, const double *q_s, double 
   ST_TRY(backsolve_impl(p, p.nw_r, p.w_qb, p.nw_dq));
   HIP_TRY(launch_axpby(p.n_dof, -1.0, p.nw_dq, 1.0, q, p.stream));
   HIP_TRY(dg_residual_on(dg, q, q_s, ns.inv_dt, p.nw_r, p.stream));
-  HIP_TRY(launch_multidot(p.nw_r, 0, 1, p.nw_r, p.n_dof, p.gm_part, p.red_blocks, p.nw_stat, p.stream));
+  HIP_TRY(launch_norm2(p.nw_r, p.n_dof, p.gm_part, p.nw_stat, p.stream));
   return SCDG_OK;
 }
 
@@ -876,7 +813,10 @@ scdg_status scdg_plan_destroy(scdg_plan *pl) {
   dfree(p.s_dense); dfree(p.dl_scale); dfree(p.dl_perm); dfree(p.dl_lbuf); dfree(p.dl_blk); dfree(p.dl_state);
   dfree(p.dl_x); dfree(p.d_dense_desc); dfree(p.d_dense_info);
   dfree(p.w_z); dfree(p.w_t); dfree(p.w_bs); dfree(p.w_qb); dfree(p.w_r); dfree(p.w_rx); dfree(p.w_dq); dfree(p.w_vec);
-  dfree(p.gm_v); dfree(p.gm_w); dfree(p.gm_z); dfree(p.gm_part); dfree(p.gm_h);
+  dfree(p.gm_v); dfree(p.gm_w); dfree(p.gm_z); dfree(p.gm_part); dfree(p.gm_h); dfree(p.kr_part);
+  if (p.kr_host) (void)hipHostFree(p.kr_host);
+  for (hipEvent_t e : p.kr_ev)
+    if (e) (void)hipEventDestroy(e);
   if (p.h_pinned) (void)hipHostFree(p.h_pinned);
   for (auto &u : p.ev_used) p.ev_pool.push_back(u.second);
   for (auto &e : p.ev_pool) {
@@ -1213,8 +1153,7 @@ scdg_status scdg_plan_create(scdg_plan **out, const scdg_structure *s, void *hip
   chk(dalloc(p, &p.gm_w, (size_t)p.n1));
   chk(dalloc(p, &p.gm_z, (size_t)p.n1));
   chk(dalloc(p, &p.diag_s, (size_t)p.n1));
-  p.red_blocks = 512;
-  chk(dalloc(p, &p.gm_part, (size_t)p.red_blocks * 64));
+  chk(dalloc(p, &p.gm_part, (size_t)kKrylovBlocks));
   chk(dalloc(p, &p.gm_h, (size_t)3 * 64));
   if (st == SCDG_OK) {
     if (hipHostMalloc(reinterpret_cast<void **>(&p.h_pinned), sizeof(double) * 3 * 64) != hipSuccess) {
@@ -1584,7 +1523,7 @@ scdg_status scdg_guess_schur_loss(scdg_plan *pl, const float *y, const float *t,
   double *e = p.w_bs, *sv = p.w_qb;
   HIP_TRY(launch_guess_err_gather(y, t, stats, p.d_bmap, p.n1, e, p.stream));
   ST_TRY(schur_apply_impl(p, e, sv));
-  HIP_TRY(launch_multidot(sv, 0, 1, sv, p.n1, p.gm_part, p.red_blocks, p.gm_h, p.stream));
+  HIP_TRY(launch_norm2(sv, p.n1, p.gm_part, p.gm_h, p.stream));
   HIP_TRY(launch_axpby(1, scale, p.gm_h, 0.0, loss, p.stream));
   if (dy) {
     HIP_TRY(launch_schur_apply_t(p, sv, p.w_t, e, fp32(p)));
