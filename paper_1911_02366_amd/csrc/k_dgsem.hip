@@ -5,20 +5,24 @@
 // Gauss-Lobatto nodes, local Lax-Friedrichs advective flux, Bassi-Rebay 1
 // viscous flux with the lifted gradient of eq. DGSEMsystem:2).
 //
-// Two launches, one workgroup per element, one thread per node:
-//   1. lifted gradient g_d (strong form):
+// Three launches:
+//   1. lifted gradient g_d (strong form), one workgroup per element:
 //        g_d = s [ sum_a D[l][a] q_a + (1/w_N) [l = N] (q^+_R - q_N)/2 - (1/w_0) [l = 0] (q^-_L - q_0)/2 ]
-//   2. residual: fluxes F_d = f^a_d(q) - f^nu_d(q, g) staged in LDS, then
+//   2. every face node's numerical flux, once:
+//        Fhat = LLF(q_L, q_R) - (f^nu(q_L, g_L) + f^nu(q_R, g_R)) / 2;
+//   3. fluxes F_d = f^a_d(q) - f^nu_d(q, g) staged in LDS, one workgroup per element, then
 //        H = J s w_i w_j w_k sum_d (1/w_l) [ sum_a Vw[l][a] F_d(a) + [l = N] Fhat_R - [l = 0] Fhat_L ]
-//      with Vw[l][a] = -w_a D[a][l] and Fhat = LLF(q_L, q_R) - (f^nu(q_L, g_L) + f^nu(q_R, g_R)) / 2.
-// A face flux is evaluated by both elements with identical arguments, so the
-// scheme stays conservative to the last bit.
+//      with Vw[l][a] = -w_a D[a][l].
+// Both elements of a face take the same Fhat, so the scheme is conservative to
+// the last bit.  Gradients and face fluxes lie in work arrays component by
+// component within an element (15 x nodes) and a direction (5 x faces), so that
+// consecutive lanes read and write consecutive values.
 //
 // The Newton matrix of eq. NewtonLinSys1 applied to a vector,
 //     A v = M v / dt + dH/dQ(Q) v,
-// runs the same two launches on dual numbers (forward-mode differentiation):
-// the lifting is linear, so the direction's gradient is the lifting of v, and
-// the residual sums carry value and derivative; only the derivative is kept.
+// runs the same launches on dual numbers (forward-mode differentiation): the
+// lifting is linear, so the direction's gradient is the lifting of v, and the
+// residual sums carry value and derivative; only the derivative is kept.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -149,74 +153,40 @@ __device__ void flux_visc(const T q[5], const T g[15], int d, const DgParams &P,
   f[4] = (a.u[0] * tau[0] + a.u[1] * tau[1] + a.u[2] * tau[2] + heat) * P.inv_re;
 }
 
-// total numerical flux through a +e_d face: LLF advective minus BR1 viscous
+// advective flux sum_d nv_d f^a_d(q) through an unnormalized face vector
 template <class T>
-__device__ void face_flux(const T ql[5], const T gl[15], const T qr[5], const T gr[15], int d,
-                          const DgParams &P, T fh[5]) {
-  T fl[5], fr[5], vl[5], vr[5];
-  flux_adv(ql, d, P.gamma, fl);
-  flux_adv(qr, d, P.gamma, fr);
-  const Prim<T> a = prim(ql, P.gamma), b = prim(qr, P.gamma);
-  const T lam_l = vabs(a.u[d]) + vsqrt(P.gamma * a.p / a.rho);
-  const T lam_r = vabs(b.u[d]) + vsqrt(P.gamma * b.p / b.rho);
-  const T lam = lam_l >= lam_r ? lam_l : lam_r;
-  flux_visc(ql, gl, d, P, vl);
-  flux_visc(qr, gr, d, P, vr);
-  for (int v = 0; v < 5; ++v)
-    fh[v] = 0.5 * (fl[v] + fr[v]) - 0.5 * lam * (qr[v] - ql[v]) - 0.5 * (vl[v] + vr[v]);
+__device__ __forceinline__ void flux_adv_normal(const Prim<T> &a, const T q[5], const double nv[3], T f[5]) {
+  const T un = a.u[0] * nv[0] + a.u[1] * nv[1] + a.u[2] * nv[2];
+  f[0] = q[0] * un;
+  for (int i = 0; i < 3; ++i) f[1 + i] = q[1 + i] * un + a.p * nv[i];
+  f[4] = un * (q[4] + a.p);
 }
 
-// total numerical flux through a +e_d face with the symmetric interior penalty
-// viscous flux: LLF advective minus
-//   {{f^nu_d(q, grad q)}} + sigma f^nu_d({{q}}, [[q]] e_d),
-// grad q the broken (element-local) gradients bl, br of the two sides and
-// [[q]] = qr - ql taken as a gradient along the face normal
+// viscous flux sum_d nv_d f^nu_d(q, g)
 template <class T>
-__device__ void face_flux_sipg(const T ql[5], const T bl[15], const T qr[5], const T br[15], int d,
-                               const DgParams &P, T fh[5]) {
-  T fl[5], fr[5], vl[5], vr[5], vp[5], qm[5], jg[15];
-  flux_adv(ql, d, P.gamma, fl);
-  flux_adv(qr, d, P.gamma, fr);
-  const Prim<T> a = prim(ql, P.gamma), b = prim(qr, P.gamma);
-  const T lam_l = vabs(a.u[d]) + vsqrt(P.gamma * a.p / a.rho);
-  const T lam_r = vabs(b.u[d]) + vsqrt(P.gamma * b.p / b.rho);
-  const T lam = lam_l >= lam_r ? lam_l : lam_r;
-  flux_visc(ql, bl, d, P, vl);
-  flux_visc(qr, br, d, P, vr);
-  for (int t = 0; t < 15; ++t) jg[t] = 0.0;
-  for (int v = 0; v < 5; ++v) {
-    qm[v] = 0.5 * (ql[v] + qr[v]);
-    jg[d * 5 + v] = qr[v] - ql[v];
+__device__ __forceinline__ void flux_visc_normal(const T q[5], const T g[15], const double nv[3], const DgParams &P,
+                                                 T f[5]) {
+  const Prim<T> a = prim(q, P.gamma);
+  const T ir = 1.0 / q[0];
+  const T eE = q[4] * ir;
+  T dv[3][3], den = 0.0;
+  for (int k = 0; k < 3; ++k) {
+    for (int i = 0; i < 3; ++i) dv[i][k] = (g[k * 5 + 1 + i] - a.u[i] * g[k * 5]) * ir;
+    den += nv[k] * ((g[k * 5 + 4] - eE * g[k * 5]) * ir - (a.u[0] * dv[0][k] + a.u[1] * dv[1][k] + a.u[2] * dv[2][k]));
   }
-  flux_visc(qm, jg, d, P, vp);
-  for (int v = 0; v < 5; ++v)
-    fh[v] = 0.5 * (fl[v] + fr[v]) - 0.5 * lam * (qr[v] - ql[v]) - 0.5 * (vl[v] + vr[v]) - P.sigma * vp[v];
-}
-
-// total numerical flux along the unnormalized face normal nv (curved faces):
-// sum_d nv_d {{f^a_d}} - lambda |nv| [[q]] / 2 - sum_d nv_d {{f^nu_d}},
-// lambda the larger of |v . nv| / |nv| + c on the two sides
-template <class T>
-__device__ void face_flux_normal(const T ql[5], const T gl[15], const T qr[5], const T gr[15],
-                                 const double nv[3], const DgParams &P, T fh[5]) {
-  const double sn = sqrt(nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2]);
-  const double inv = 1.0 / sn;
-  const Prim<T> a = prim(ql, P.gamma), b = prim(qr, P.gamma);
-  const T un_l = (a.u[0] * nv[0] + a.u[1] * nv[1] + a.u[2] * nv[2]) * inv;
-  const T un_r = (b.u[0] * nv[0] + b.u[1] * nv[1] + b.u[2] * nv[2]) * inv;
-  const T lam_l = vabs(un_l) + vsqrt(P.gamma * a.p / a.rho);
-  const T lam_r = vabs(un_r) + vsqrt(P.gamma * b.p / b.rho);
-  const T lam = lam_l >= lam_r ? lam_l : lam_r;
-  T acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int d = 0; d < 3; ++d) {
-    T fl[5], fr[5], vl[5], vr[5];
-    flux_adv(ql, d, P.gamma, fl);
-    flux_adv(qr, d, P.gamma, fr);
-    flux_visc(ql, gl, d, P, vl);
-    flux_visc(qr, gr, d, P, vr);
-    for (int v = 0; v < 5; ++v) acc[v] += nv[d] * (0.5 * (fl[v] + fr[v]) - 0.5 * (vl[v] + vr[v]));
+  const T temp = P.gamma * P.mach2 * a.p / q[0];
+  const T mu = (1.0 + P.suth) / (temp + P.suth) * temp * vsqrt(temp);
+  const T div = dv[0][0] + dv[1][1] + dv[2][2];
+  f[0] = 0.0;
+  T work = 0.0;
+  for (int i = 0; i < 3; ++i) {
+    T t = 0.0;
+    for (int d = 0; d < 3; ++d) t += nv[d] * (dv[i][d] + dv[d][i]);
+    t = mu * (t - (2.0 / 3.0) * nv[i] * div);
+    f[1 + i] = t * P.inv_re;
+    work += a.u[i] * t;
   }
-  for (int v = 0; v < 5; ++v) fh[v] = acc[v] - 0.5 * lam * sn * (qr[v] - ql[v]);
+  f[4] = (work + mu * P.gamma / P.prandtl * den) * P.inv_re;
 }
 
 // cooperative copy of the parameter block into LDS (ends with a barrier)
@@ -240,399 +210,332 @@ __device__ __forceinline__ int node_with(int node, int p, int d, int l) {
   return c[0] + p * c[1] + p * p * c[2];
 }
 
-// BR1 lifted gradient g; with gb != NULL also the broken gradient of each
-// element's own interpolant (the same line derivatives without the surface term)
-__global__ __launch_bounds__(512) void lift_kernel(const DgParams *__restrict__ prm, const double *__restrict__ q,
-                            double *__restrict__ g, double *__restrict__ gb) {
+// index of component t of the gradient work arrays at a node
+template <int PP>
+__device__ __forceinline__ int64_t g_at(int64_t e, int t, int node) {
+  return (e * 15 + t) * (PP * PP * PP) + node;
+}
+
+// Lifted gradient of one field (blockIdx.y 0) or of a field and a direction
+// (0 and 1); gb, when given, also takes the broken gradient of each element's own
+// interpolant (the same line derivatives without the surface term).
+//   Bound by the gradient's 15 doubles per node: 512 000 nodes of order 4 (82 MB
+// for a field) 21 us, 41 us for two (52 and 104 us with node-by-node stores 120
+// bytes apart and the order not known to the compiler).
+struct LiftArgs {
+  const double *q[2];
+  double *g[2], *gb[2];
+};
+
+template <int PP>
+__global__ __launch_bounds__((PP * PP * PP + 63) / 64 * 64) void lift_kernel(const DgParams *__restrict__ prm,
+                                                                             LiftArgs a) {
+  constexpr int P3 = PP * PP * PP, N = PP - 1;
   __shared__ DgParams P;
-  __shared__ double qs[kMaxP * kMaxP * kMaxP * 5];
+  __shared__ double qs[P3 * 5];
   load_params(prm, &P);
-  const int p = P.p, p3 = p * p * p, n = p - 1;
-  const int e = blockIdx.x;
-  const double *qe = q + (int64_t)e * p3 * 5;
-  for (int t = threadIdx.x; t < p3 * 5; t += blockDim.x) qs[t] = qe[t];
+  const int e = blockIdx.x, f = blockIdx.y;
+  const double *__restrict__ q = a.q[f];
+  double *__restrict__ g = a.g[f];
+  double *__restrict__ gb = a.gb[f];
+  const double *__restrict__ qe = q + (int64_t)e * P3 * 5;
+  for (int t = threadIdx.x; t < P3 * 5; t += blockDim.x) qs[t] = qe[t];
   __syncthreads();
   const int node = threadIdx.x;
-  if (node >= p3) return;
-  const int c[3] = {node % p, (node / p) % p, node / (p * p)};
-  double out[15];
+  if (node >= P3) return;
+  const int c[3] = {node % PP, (node / PP) % PP, node / (PP * PP)};
+#pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const int l = c[d];
-    for (int v = 0; v < 5; ++v) {
-      double acc = 0.0;
-      for (int a = 0; a < p; ++a) acc += P.d[l][a] * qs[node_with(node, p, d, a) * 5 + v];
-      out[d * 5 + v] = acc;
+    constexpr int strides[3] = {1, PP, PP * PP};
+    const int st = strides[d], l = c[d];
+    const double *line = qs + (node - l * st) * 5;
+    double out[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int b = 0; b < PP; ++b) {
+      const double dl = P.d[l][b];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) out[v] += dl * line[b * st * 5 + v];
     }
-    if (gb) {
-      double *gbe = gb + ((int64_t)e * p3 + node) * 15 + d * 5;
-      for (int v = 0; v < 5; ++v) gbe[v] = P.s * out[d * 5 + v];
+    if (gb)
+      for (int v = 0; v < 5; ++v) gb[g_at<PP>(e, d * 5 + v, node)] = P.s * out[v];
+    if (l == N || l == 0) {
+      const double *qn = q + ((int64_t)nbr_elem(e, P.k_elem, d, l == N ? 1 : -1) * P3 + node + (l == N ? -N : N) * st) * 5;
+      const double f2 = l == N ? 0.5 / P.w[N] : -0.5 / P.w[0];
+      for (int v = 0; v < 5; ++v) out[v] += f2 * (qn[v] - qs[node * 5 + v]);
     }
-    if (l == n) {
-      const double *qn = q + ((int64_t)nbr_elem(e, P.k_elem, d, 1) * p3 + node_with(node, p, d, 0)) * 5;
-      for (int v = 0; v < 5; ++v) out[d * 5 + v] += (0.5 / P.w[n]) * (qn[v] - qs[node * 5 + v]);
-    }
-    if (l == 0) {
-      const double *qn = q + ((int64_t)nbr_elem(e, P.k_elem, d, -1) * p3 + node_with(node, p, d, n)) * 5;
-      for (int v = 0; v < 5; ++v) out[d * 5 + v] -= (0.5 / P.w[0]) * (qn[v] - qs[node * 5 + v]);
-    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) g[g_at<PP>(e, d * 5 + v, node)] = P.s * out[v];
   }
-  double *ge = g + ((int64_t)e * p3 + node) * 15;
-  for (int t = 0; t < 15; ++t) ge[t] = P.s * out[t];
 }
 
 // Lifted gradient on curved elements (metric met: 10 doubles per node, (J a^i)_n
 // at 3 i + n and J at 9):
 //   g_n = (1/J) sum_i [ sum_a D[l][a] ((J a^i)_n q)_a
 //                      + (1/w_N) [l = N] (J a^i)_n (q^+ - q) / 2 - (1/w_0) [l = 0] (J a^i)_n (q^- - q) / 2 ]
-__global__ __launch_bounds__(512) void lift_curved_kernel(const DgParams *__restrict__ prm,
-                                                          const double *__restrict__ q,
-                                                          const double *__restrict__ met,
-                                                          double *__restrict__ g) {
+template <int PP>
+__global__ __launch_bounds__((PP * PP * PP + 63) / 64 * 64) void lift_curved_kernel(const DgParams *__restrict__ prm,
+                                                                                    const double *__restrict__ met,
+                                                                                    LiftArgs a) {
+  constexpr int P3 = PP * PP * PP, N = PP - 1;
   __shared__ DgParams P;
-  __shared__ double qs[kMaxP * kMaxP * kMaxP * 5];
-  extern __shared__ double ms[];   // [p3][10] metric of the element
+  __shared__ double qs[P3 * 5], ms[P3 * 10];
   load_params(prm, &P);
-  const int p = P.p, p3 = p * p * p, n = p - 1;
-  const int e = blockIdx.x;
-  const double *qe = q + (int64_t)e * p3 * 5;
-  const double *me = met + (int64_t)e * p3 * 10;
-  for (int t = threadIdx.x; t < p3 * 5; t += blockDim.x) qs[t] = qe[t];
-  for (int t = threadIdx.x; t < p3 * 10; t += blockDim.x) ms[t] = me[t];
+  const int e = blockIdx.x, f = blockIdx.y;
+  const double *__restrict__ q = a.q[f];
+  double *__restrict__ g = a.g[f];
+  const double *__restrict__ qe = q + (int64_t)e * P3 * 5;
+  const double *__restrict__ me = met + (int64_t)e * P3 * 10;
+  for (int t = threadIdx.x; t < P3 * 5; t += blockDim.x) qs[t] = qe[t];
+  for (int t = threadIdx.x; t < P3 * 10; t += blockDim.x) ms[t] = me[t];
   __syncthreads();
   const int node = threadIdx.x;
-  if (node >= p3) return;
-  const int c[3] = {node % p, (node / p) % p, node / (p * p)};
+  if (node >= P3) return;
+  const int c[3] = {node % PP, (node / PP) % PP, node / (PP * PP)};
   double out[15];
+#pragma unroll
   for (int t = 0; t < 15; ++t) out[t] = 0.0;
+#pragma unroll
   for (int i = 0; i < 3; ++i) {
-    const int l = c[i];
-    for (int a = 0; a < p; ++a) {
-      const int na = node_with(node, p, i, a);
-      const double dl = P.d[l][a];
+    constexpr int strides[3] = {1, PP, PP * PP};
+    const int st = strides[i], l = c[i], first = node - l * st;
+#pragma unroll
+    for (int b = 0; b < PP; ++b) {
+      const int na = first + b * st;
+      const double dl = P.d[l][b];
+#pragma unroll
       for (int m = 0; m < 3; ++m) {
-        const double f = dl * ms[na * 10 + 3 * i + m];
-        for (int v = 0; v < 5; ++v) out[m * 5 + v] += f * qs[na * 5 + v];
+        const double w = dl * ms[na * 10 + 3 * i + m];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) out[m * 5 + v] += w * qs[na * 5 + v];
       }
     }
-    if (l == n || l == 0) {
-      const int step = l == n ? 1 : -1;
-      const double *qn = q + ((int64_t)nbr_elem(e, P.k_elem, i, step) * p3 + node_with(node, p, i, l == n ? 0 : n)) * 5;
-      const double sgn = l == n ? 0.5 / P.w[n] : -0.5 / P.w[0];
+    if (l == N || l == 0) {
+      const double *qn = q + ((int64_t)nbr_elem(e, P.k_elem, i, l == N ? 1 : -1) * P3 + node + (l == N ? -N : N) * st) * 5;
+      const double sgn = l == N ? 0.5 / P.w[N] : -0.5 / P.w[0];
+      double jump[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) jump[v] = qn[v] - qs[node * 5 + v];
+#pragma unroll
       for (int m = 0; m < 3; ++m) {
-        const double f = sgn * ms[node * 10 + 3 * i + m];
-        for (int v = 0; v < 5; ++v) out[m * 5 + v] += f * (qn[v] - qs[node * 5 + v]);
+        const double w = sgn * ms[node * 10 + 3 * i + m];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) out[m * 5 + v] += w * jump[v];
       }
     }
   }
   const double inv_j = 1.0 / ms[node * 10 + 9];
-  double *ge = g + ((int64_t)e * p3 + node) * 15;
-  for (int t = 0; t < 15; ++t) ge[t] = inv_j * out[t];
+#pragma unroll
+  for (int t = 0; t < 15; ++t) g[g_at<PP>(e, t, node)] = inv_j * out[t];
 }
 
-// Residual on curved elements: contravariant fluxes F^i = sum_n (J a^i)_n f_n in
-// LDS, the weak volume term and the face fluxes along J a^i of this element's
-// face node, mass J w_i w_j w_k:
-//   H = w_i w_j w_k sum_i (1/w_l) [ sum_a Vw[l][a] F^i(a) + [l = N] Fhat_R - [l = 0] Fhat_L ]
-//
-// With T = Dual the same sums give the directional derivative: q and g carry
-// the direction dq and the lifted gradient of dq (the lifting is linear), and
-// r = M inv_dt dq + dH/dQ(q) dq (q_s unused).
-template <class T>
-__global__ __launch_bounds__(512) void residual_curved_kernel(const DgParams *__restrict__ prm,
-                                                              const double *__restrict__ q,
-                                                              const double *__restrict__ dq,
-                                                              const double *__restrict__ g,
-                                                              const double *__restrict__ dg,
-                                                              const double *__restrict__ met,
-                                                              const double *__restrict__ q_s, double inv_dt,
-                                                              double *__restrict__ r) {
-  __shared__ DgParams P;
-  extern __shared__ double fs[];   // [3][p3][5] contravariant fluxes
-  load_params(prm, &P);
-  const int p = P.p, p3 = p * p * p, n = p - 1;
-  const int e = blockIdx.x;
-  const int node = threadIdx.x;
-  const bool live = node < p3;
-  T qn[5], gn[15];
-  double mn[10];
-  if (live) {
-    const int64_t id = (int64_t)e * p3 + node;
-    for (int v = 0; v < 5; ++v) qn[v] = at<T>(q, dq, id * 5 + v);
-    for (int t = 0; t < 15; ++t) gn[t] = at<T>(g, dg, id * 15 + t);
-    for (int t = 0; t < 10; ++t) mn[t] = met[id * 10 + t];
-    double ft[3][5];
-    for (int i = 0; i < 3; ++i)
-      for (int v = 0; v < 5; ++v) ft[i][v] = 0.0;
-    for (int d = 0; d < 3; ++d) {
-      T fa[5], fv[5];
-      flux_adv(qn, d, P.gamma, fa);
-      flux_visc(qn, gn, d, P, fv);
-      for (int i = 0; i < 3; ++i)
-        for (int v = 0; v < 5; ++v) ft[i][v] += mn[3 * i + d] * part(fa[v] - fv[v]);
-    }
-    for (int i = 0; i < 3; ++i)
-      for (int v = 0; v < 5; ++v) fs[(i * p3 + node) * 5 + v] = ft[i][v];
-  }
-  __syncthreads();
-  if (!live) return;
-  const int c[3] = {node % p, (node / p) % p, node / (p * p)};
-  double h[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int i = 0; i < 3; ++i) {
-    const int l = c[i];
-    double rd[5];
-    for (int v = 0; v < 5; ++v) {
-      double acc = 0.0;
-      for (int a = 0; a < p; ++a) acc += P.vw[l][a] * fs[(i * p3 + node_with(node, p, i, a)) * 5 + v];
-      rd[v] = acc;
-    }
-    const double nv[3] = {mn[3 * i], mn[3 * i + 1], mn[3 * i + 2]};
-    if (l == n) {
-      const int64_t nb = (int64_t)nbr_elem(e, P.k_elem, i, 1) * p3 + node_with(node, p, i, 0);
-      T qb[5], gb[15], fh[5];
-      for (int v = 0; v < 5; ++v) qb[v] = at<T>(q, dq, nb * 5 + v);
-      for (int t = 0; t < 15; ++t) gb[t] = at<T>(g, dg, nb * 15 + t);
-      face_flux_normal(qn, gn, qb, gb, nv, P, fh);
-      for (int v = 0; v < 5; ++v) rd[v] += part(fh[v]);
-    }
-    if (l == 0) {
-      const int64_t nb = (int64_t)nbr_elem(e, P.k_elem, i, -1) * p3 + node_with(node, p, i, n);
-      T qb[5], gb[15], fh[5];
-      for (int v = 0; v < 5; ++v) qb[v] = at<T>(q, dq, nb * 5 + v);
-      for (int t = 0; t < 15; ++t) gb[t] = at<T>(g, dg, nb * 15 + t);
-      face_flux_normal(qb, gb, qn, gn, nv, P, fh);
-      for (int v = 0; v < 5; ++v) rd[v] -= part(fh[v]);
-    }
-    for (int v = 0; v < 5; ++v) h[v] += rd[v] / P.w[l];
-  }
-  const double w3 = P.w[c[0]] * P.w[c[1]] * P.w[c[2]];
-  const double m = mn[9] * w3;
-  const int64_t id = (int64_t)e * p3 + node;
-  double *re = r + id * 5;
-  for (int v = 0; v < 5; ++v) {
-    double val = w3 * h[v];
-    if constexpr (std::is_same<T, Dual>::value) {
-      val += m * inv_dt * dq[id * 5 + v];
-    } else {
-      if (q_s) val += m * inv_dt * (qn[v] - q_s[id * 5 + v]);
-    }
-    re[v] = val;
-  }
-}
+// What the operator's kernels read and write (the direction's arrays only with
+// T = Dual; gb, dgb the broken gradients of the interior-penalty flux).
+struct DgArgs {
+  const double *q, *dq, *g, *dg, *gb, *dgb, *met, *q_s;
+  double *face;       // numerical fluxes (of T = Dual: their derivatives), [3][5][faces of a direction]
+  double *r;
+  double inv_dt;
+  int64_t n_pairs;    // faces of a direction: n_elem P^2
+};
 
-// With T = Dual: r = M inv_dt dq + dH/dQ(q) dq, dg the lifted gradient of dq.
-// SIPG: the face viscous flux is the interior-penalty flux on the broken
-// gradients gbq (dgb for the direction); a template argument, so that the
-// Bassi-Rebay 1 kernels carry none of its code.
-template <class T, bool SIPG>
-__global__ __launch_bounds__(512) void residual_kernel(const DgParams *__restrict__ prm, const double *__restrict__ q,
-                                const double *__restrict__ dq, const double *__restrict__ g,
-                                const double *__restrict__ dg, const double *__restrict__ gbq,
-                                const double *__restrict__ dgb, const double *__restrict__ q_s,
-                                double inv_dt, double *__restrict__ r) {
-  __shared__ DgParams P;
-  extern __shared__ double fs[];   // [3][p3][5] volume fluxes
-  load_params(prm, &P);
-  const int p = P.p, p3 = p * p * p, n = p - 1;
-  const int e = blockIdx.x;
-  const int node = threadIdx.x;
-  const bool live = node < p3;
-  T qn[5], gn[15];
-  if (live) {
-    const int64_t id = (int64_t)e * p3 + node;
-    for (int v = 0; v < 5; ++v) qn[v] = at<T>(q, dq, id * 5 + v);
-    for (int t = 0; t < 15; ++t) gn[t] = at<T>(g, dg, id * 15 + t);
-    for (int d = 0; d < 3; ++d) {
-      T fa[5], fv[5];
-      flux_adv(qn, d, P.gamma, fa);
-      flux_visc(qn, gn, d, P, fv);
-      for (int v = 0; v < 5; ++v) fs[(d * p3 + node) * 5 + v] = part(fa[v] - fv[v]);
-    }
-  }
-  __syncthreads();
-  if (!live) return;
-  const int c[3] = {node % p, (node / p) % p, node / (p * p)};
-  double h[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int d = 0; d < 3; ++d) {
-    const int l = c[d];
-    double rd[5];
-    for (int v = 0; v < 5; ++v) {
-      double acc = 0.0;
-      for (int a = 0; a < p; ++a) acc += P.vw[l][a] * fs[(d * p3 + node_with(node, p, d, a)) * 5 + v];
-      rd[v] = acc;
-    }
-    if (l == n) {
-      const int64_t nb = (int64_t)nbr_elem(e, P.k_elem, d, 1) * p3 + node_with(node, p, d, 0);
-      T qb[5], gb[15], fh[5];
-      for (int v = 0; v < 5; ++v) qb[v] = at<T>(q, dq, nb * 5 + v);
-      if constexpr (SIPG) {
-        T bn[15];
-        for (int t = 0; t < 15; ++t) bn[t] = at<T>(gbq, dgb, ((int64_t)e * p3 + node) * 15 + t);
-        for (int t = 0; t < 15; ++t) gb[t] = at<T>(gbq, dgb, nb * 15 + t);
-        face_flux_sipg(qn, bn, qb, gb, d, P, fh);
-      } else {
-        for (int t = 0; t < 15; ++t) gb[t] = at<T>(g, dg, nb * 15 + t);
-        face_flux(qn, gn, qb, gb, d, P, fh);
-      }
-      for (int v = 0; v < 5; ++v) rd[v] += part(fh[v]);
-    }
-    if (l == 0) {
-      const int64_t nb = (int64_t)nbr_elem(e, P.k_elem, d, -1) * p3 + node_with(node, p, d, n);
-      T qb[5], gb[15], fh[5];
-      for (int v = 0; v < 5; ++v) qb[v] = at<T>(q, dq, nb * 5 + v);
-      if constexpr (SIPG) {
-        T bn[15];
-        for (int t = 0; t < 15; ++t) bn[t] = at<T>(gbq, dgb, ((int64_t)e * p3 + node) * 15 + t);
-        for (int t = 0; t < 15; ++t) gb[t] = at<T>(gbq, dgb, nb * 15 + t);
-        face_flux_sipg(qb, gb, qn, bn, d, P, fh);
-      } else {
-        for (int t = 0; t < 15; ++t) gb[t] = at<T>(g, dg, nb * 15 + t);
-        face_flux(qb, gb, qn, gn, d, P, fh);
-      }
-      for (int v = 0; v < 5; ++v) rd[v] -= part(fh[v]);
-    }
-    for (int v = 0; v < 5; ++v) h[v] += rd[v] / P.w[l];
-  }
-  const double m = P.jac * P.w[c[0]] * P.w[c[1]] * P.w[c[2]];
-  const int64_t id = (int64_t)e * p3 + node;
-  double *re = r + id * 5;
-  for (int v = 0; v < 5; ++v) {
-    double val = m * P.s * h[v];
-    if constexpr (std::is_same<T, Dual>::value) {
-      val += m * inv_dt * dq[id * 5 + v];
-    } else {
-      if (q_s) val += m * inv_dt * (qn[v] - q_s[id * 5 + v]);
-    }
-    re[v] = val;
-  }
-}
+enum FaceKind { kFaceBr1 = 0, kFaceSipg = 1, kFaceCurved = 2 };
 
-// The same operator in two parts, for the Newton-matrix product on dual
-// numbers, where the fused kernel holds a node's state, gradient, its face
-// neighbour's state and gradient and the flux temporaries at once and spills:
-//   volume_kernel: r = M inv_dt dq + the volume sums (every node);
-//   face_kernel (one launch per direction d): every +e_d face node pair
-//     evaluates its numerical flux once and adds it to the node on the
-//     minus side and subtracts it from the node on the plus side.
-// Within one launch no two face pairs share a node; the launches follow each
-// other on the stream.  Equal to residual_kernel up to the order of the sums.
-template <class T>
-__global__ __launch_bounds__(512) void volume_kernel(const DgParams *__restrict__ prm, const double *__restrict__ q,
-                                                     const double *__restrict__ dq, const double *__restrict__ g,
-                                                     const double *__restrict__ dg, const double *__restrict__ q_s,
-                                                     double inv_dt, double *__restrict__ r) {
-  __shared__ DgParams P;
-  extern __shared__ double fs[];   // [3][p3][5] volume fluxes
-  load_params(prm, &P);
-  const int p = P.p, p3 = p * p * p;
-  const int e = blockIdx.x;
-  const int node = threadIdx.x;
-  const bool live = node < p3;
-  const int64_t id = (int64_t)e * p3 + node;
-  if (live) {
-    T qn[5], gn[15];
-    for (int v = 0; v < 5; ++v) qn[v] = at<T>(q, dq, id * 5 + v);
-    for (int t = 0; t < 15; ++t) gn[t] = at<T>(g, dg, id * 15 + t);
-    for (int d = 0; d < 3; ++d) {
-      T fa[5], fv[5];
-      flux_adv(qn, d, P.gamma, fa);
-      flux_visc(qn, gn, d, P, fv);
-      for (int v = 0; v < 5; ++v) fs[(d * p3 + node) * 5 + v] = part(fa[v] - fv[v]);
-    }
+// The numerical flux of every +xi_D face node, once: Lax-Friedrichs advective
+// minus {{f^nu(q, grad q)}} along the face vector (e_D, or J a^D of the element on
+// the minus side; the plus side's differs in rounding alone), grad q the lifted
+// gradient, or the broken one with the penalty term sigma f^nu({{q}}, [[q]] e_D),
+// [[q]] = q^+ - q^- taken as a gradient along the normal.  The terms are taken one
+// side's gradient at a time, which keeps the registers of the dual-number form
+// down.
+template <class T, int PP, int KIND, int D>
+__device__ __forceinline__ void face_flux_body(const DgParams &P, const DgArgs &a, int64_t idx) {
+  constexpr int P2 = PP * PP, P3 = P2 * PP, N = PP - 1;
+  constexpr int strides[3] = {1, PP, P2};
+  const int64_t e = idx / P2;
+  const int tt = (int)(idx - e * P2), t1 = tt % PP, t2 = tt / PP;
+  // transverse directions of D in increasing order take (t1, t2)
+  constexpr int S1 = strides[D == 0 ? 1 : 0], S2 = strides[D == 2 ? 1 : 2];
+  const int nr = t1 * S1 + t2 * S2, nl = nr + N * strides[D];
+  const int64_t er = nbr_elem((int)e, P.k_elem, D, 1);
+  const int64_t il = e * P3 + nl, ir = er * P3 + nr;
+  double nv[3] = {D == 0 ? 1.0 : 0.0, D == 1 ? 1.0 : 0.0, D == 2 ? 1.0 : 0.0};
+  double sn = 1.0;
+  if (KIND == kFaceCurved) {
+    for (int m = 0; m < 3; ++m) nv[m] = a.met[il * 10 + 3 * D + m];
+    sn = sqrt(nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2]);
   }
-  __syncthreads();
-  if (!live) return;
-  const int c[3] = {node % p, (node / p) % p, node / (p * p)};
-  double h[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int d = 0; d < 3; ++d) {
-    const int l = c[d];
-    for (int v = 0; v < 5; ++v) {
-      double acc = 0.0;
-      for (int a = 0; a < p; ++a) acc += P.vw[l][a] * fs[(d * p3 + node_with(node, p, d, a)) * 5 + v];
-      h[v] += acc / P.w[l];
-    }
-  }
-  const double m = P.jac * P.w[c[0]] * P.w[c[1]] * P.w[c[2]];
-  double *re = r + id * 5;
-  for (int v = 0; v < 5; ++v) {
-    double val = m * P.s * h[v];
-    if constexpr (std::is_same<T, Dual>::value) {
-      val += m * inv_dt * dq[id * 5 + v];
-    } else {
-      if (q_s) val += m * inv_dt * (q[id * 5 + v] - q_s[id * 5 + v]);
-    }
-    re[v] = val;
-  }
-}
-
-template <class T, bool SIPG, int d>
-__global__ __launch_bounds__(256) void face_kernel(const DgParams *__restrict__ prm, int64_t n_pairs,
-                                                   const double *__restrict__ q, const double *__restrict__ dq,
-                                                   const double *__restrict__ g, const double *__restrict__ dg,
-                                                   const double *__restrict__ gbq, const double *__restrict__ dgb,
-                                                   double *__restrict__ r) {
-  __shared__ DgParams P;
-  load_params(prm, &P);
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n_pairs) return;
-  const int p = P.p, p2 = p * p, p3 = p2 * p, n = p - 1;
-  const int e = (int)(idx / p2), tt = (int)(idx % p2), t1 = tt % p, t2 = tt / p;
-  // transverse directions of d in increasing order take (t1, t2)
-  int c[3];
-  c[d] = n;
-  c[d == 0 ? 1 : 0] = t1;
-  c[d == 2 ? 1 : 2] = t2;
-  const int node_l = c[0] + p * c[1] + p2 * c[2];
-  const int node_r = node_with(node_l, p, d, 0);
-  const int64_t il = (int64_t)e * p3 + node_l;
-  const int64_t ir = (int64_t)nbr_elem(e, P.k_elem, d, 1) * p3 + node_r;
-  // the flux term by term, one side's gradient live at a time (fewer registers
-  // than face_flux / face_flux_sipg, the same terms)
   T ql[5], qr[5], fh[5];
+#pragma unroll
   for (int v = 0; v < 5; ++v) {
-    ql[v] = at<T>(q, dq, il * 5 + v);
-    qr[v] = at<T>(q, dq, ir * 5 + v);
+    ql[v] = at<T>(a.q, a.dq, il * 5 + v);
+    qr[v] = at<T>(a.q, a.dq, ir * 5 + v);
   }
-  const double *gsrc = SIPG ? gbq : g, *dgsrc = SIPG ? dgb : dg;
+  const double *gsrc = KIND == kFaceSipg ? a.gb : a.g, *dgsrc = KIND == kFaceSipg ? a.dgb : a.dg;
+  auto visc = [&](const T *qq, const T *gs, T *fv) {
+    if (KIND == kFaceCurved) flux_visc_normal(qq, gs, nv, P, fv);
+    else flux_visc(qq, gs, D, P, fv);
+  };
   {
     T gs[15], fv[5];
-    for (int t = 0; t < 15; ++t) gs[t] = at<T>(gsrc, dgsrc, il * 15 + t);
-    flux_visc(ql, gs, d, P, fv);
+#pragma unroll
+    for (int t = 0; t < 15; ++t) gs[t] = at<T>(gsrc, dgsrc, g_at<PP>(e, t, nl));
+    visc(ql, gs, fv);
+#pragma unroll
     for (int v = 0; v < 5; ++v) fh[v] = -0.5 * fv[v];
   }
   {
     T gs[15], fv[5];
-    for (int t = 0; t < 15; ++t) gs[t] = at<T>(gsrc, dgsrc, ir * 15 + t);
-    flux_visc(qr, gs, d, P, fv);
+#pragma unroll
+    for (int t = 0; t < 15; ++t) gs[t] = at<T>(gsrc, dgsrc, g_at<PP>(er, t, nr));
+    visc(qr, gs, fv);
+#pragma unroll
     for (int v = 0; v < 5; ++v) fh[v] -= 0.5 * fv[v];
   }
-  if constexpr (SIPG) {
+  if constexpr (KIND == kFaceSipg) {
     T qm[5], jg[15], fv[5];
     for (int t = 0; t < 15; ++t) jg[t] = 0.0;
     for (int v = 0; v < 5; ++v) {
       qm[v] = 0.5 * (ql[v] + qr[v]);
-      jg[d * 5 + v] = qr[v] - ql[v];
+      jg[D * 5 + v] = qr[v] - ql[v];
     }
-    flux_visc(qm, jg, d, P, fv);
+    flux_visc(qm, jg, D, P, fv);
     for (int v = 0; v < 5; ++v) fh[v] -= P.sigma * fv[v];
   }
   {
-    T fa[5];
-    flux_adv(ql, d, P.gamma, fa);
+    const Prim<T> b = prim(ql, P.gamma), c = prim(qr, P.gamma);
+    T fa[5], un_l = b.u[D], un_r = c.u[D];
+    if constexpr (KIND == kFaceCurved) {
+      const double inv = 1.0 / sn;
+      un_l = (b.u[0] * nv[0] + b.u[1] * nv[1] + b.u[2] * nv[2]) * inv;
+      un_r = (c.u[0] * nv[0] + c.u[1] * nv[1] + c.u[2] * nv[2]) * inv;
+      flux_adv_normal(b, ql, nv, fa);
+    } else {
+      flux_adv(ql, D, P.gamma, fa);
+    }
     for (int v = 0; v < 5; ++v) fh[v] += 0.5 * fa[v];
-    flux_adv(qr, d, P.gamma, fa);
+    if constexpr (KIND == kFaceCurved) flux_adv_normal(c, qr, nv, fa);
+    else flux_adv(qr, D, P.gamma, fa);
     for (int v = 0; v < 5; ++v) fh[v] += 0.5 * fa[v];
-    const Prim<T> a = prim(ql, P.gamma), b = prim(qr, P.gamma);
-    const T lam_l = vabs(a.u[d]) + vsqrt(P.gamma * a.p / a.rho);
-    const T lam_r = vabs(b.u[d]) + vsqrt(P.gamma * b.p / b.rho);
+    const T lam_l = vabs(un_l) + vsqrt(P.gamma * b.p / b.rho);
+    const T lam_r = vabs(un_r) + vsqrt(P.gamma * c.p / c.rho);
     const T lam = lam_l >= lam_r ? lam_l : lam_r;
-    for (int v = 0; v < 5; ++v) fh[v] -= 0.5 * lam * (qr[v] - ql[v]);
+    for (int v = 0; v < 5; ++v) fh[v] -= 0.5 * lam * sn * (qr[v] - ql[v]);
   }
-  const double cf = P.jac * P.s * P.w[t1] * P.w[t2];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) a.face[(D * 5 + v) * a.n_pairs + idx] = part(fh[v]);
+}
+
+// blockIdx.y: the direction (a template argument of the body, whose flux code
+// indexes arrays by it).  One launch for the three: each alone ended in a tail of
+// half-empty compute units, and the residual was read and written three times.
+template <class T, int PP, int KIND>
+__global__ __launch_bounds__(256) void face_flux_kernel(const DgParams *__restrict__ prm, DgArgs a) {
+  __shared__ DgParams P;
+  load_params(prm, &P);
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= a.n_pairs) return;
+  if (blockIdx.y == 0) face_flux_body<T, PP, KIND, 0>(P, a, idx);
+  else if (blockIdx.y == 1) face_flux_body<T, PP, KIND, 1>(P, a, idx);
+  else face_flux_body<T, PP, KIND, 2>(P, a, idx);
+}
+
+// The volume sums and the element's face fluxes.  Curved elements: contravariant
+// fluxes F^i = sum_n (J a^i)_n f_n and the mass J w_i w_j w_k,
+//   H = w_i w_j w_k sum_i (1/w_l) [ sum_a Vw[l][a] F^i(a) + [l = N] Fhat_R - [l = 0] Fhat_L ].
+// With T = Dual: r = M inv_dt dq + dH/dQ(q) dq, else r = M inv_dt (q - q_s) + H(q)
+// (q_s null: H alone).
+template <class T, int PP, bool CURVED>
+__global__ __launch_bounds__((PP * PP * PP + 63) / 64 * 64) void volume_kernel(const DgParams *__restrict__ prm,
+                                                                               DgArgs a) {
+  constexpr int P2 = PP * PP, P3 = P2 * PP, N = PP - 1;
+  __shared__ DgParams P;
+  __shared__ double fs[3 * P3 * 5];
+  load_params(prm, &P);
+  const int64_t e = blockIdx.x;
+  const int node = threadIdx.x;
+  const bool live = node < P3;
+  const int64_t id = e * P3 + node;
+  double mass = 0.0;
+  if (live) {
+    T qn[5], gn[15];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) qn[v] = at<T>(a.q, a.dq, id * 5 + v);
+#pragma unroll
+    for (int t = 0; t < 15; ++t) gn[t] = at<T>(a.g, a.dg, g_at<PP>(e, t, node));
+    if constexpr (CURVED) {
+      const Prim<T> b = prim(qn, P.gamma);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        double nv[3];
+        for (int m = 0; m < 3; ++m) nv[m] = a.met[id * 10 + 3 * i + m];
+        T fa[5], fv[5];
+        flux_adv_normal(b, qn, nv, fa);
+        flux_visc_normal(qn, gn, nv, P, fv);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) fs[(i * P3 + node) * 5 + v] = part(fa[v] - fv[v]);
+      }
+      mass = a.met[id * 10 + 9];
+    } else {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        T fa[5], fv[5];
+        flux_adv(qn, d, P.gamma, fa);
+        flux_visc(qn, gn, d, P, fv);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) fs[(d * P3 + node) * 5 + v] = part(fa[v] - fv[v]);
+      }
+    }
+  }
+  __syncthreads();
+  if (!live) return;
+  const int c[3] = {node % PP, (node / PP) % PP, node / P2};
+  double h[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    constexpr int strides[3] = {1, PP, P2};
+    const int st = strides[d], l = c[d];
+    const double *line = fs + (d * P3 + node - l * st) * 5;
+    double rd[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int b = 0; b < PP; ++b) {
+      const double vw = P.vw[l][b];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) rd[v] += vw * line[b * st * 5 + v];
+    }
+    if (l == N || l == 0) {
+      // the +d face of this element, or of its neighbour on the minus side
+      const int64_t ef = l == N ? e : nbr_elem((int)e, P.k_elem, d, -1);
+      const int t1 = c[d == 0 ? 1 : 0], t2 = c[d == 2 ? 1 : 2];
+      const double *fh = a.face + d * 5 * a.n_pairs + ef * P2 + t1 + PP * t2;
+      const double sg = l == N ? 1.0 : -1.0;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) rd[v] += sg * fh[v * a.n_pairs];
+    }
+    const double iw = 1.0 / P.w[l];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) h[v] += rd[v] * iw;
+  }
+  const double w3 = P.w[c[0]] * P.w[c[1]] * P.w[c[2]];
+  const double m = CURVED ? mass * w3 : P.jac * w3;
+  const double hs = CURVED ? w3 : m * P.s;
+#pragma unroll
   for (int v = 0; v < 5; ++v) {
-    const double f = cf * part(fh[v]);
-    r[il * 5 + v] += f;
-    r[ir * 5 + v] -= f;
+    double val = hs * h[v];
+    if constexpr (std::is_same<T, Dual>::value) {
+      val += m * a.inv_dt * a.dq[id * 5 + v];
+    } else {
+      if (a.q_s) val += m * a.inv_dt * (a.q[id * 5 + v] - a.q_s[id * 5 + v]);
+    }
+    a.r[id * 5 + v] = val;
   }
+}
+
+// the lifted gradient node by node (15 doubles), for the caller
+__global__ void gradient_export_kernel(const double *__restrict__ g, int64_t n_nodes, int p3, double *__restrict__ out) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= n_nodes * 15) return;
+  const int64_t id = i / 15, e = id / p3;
+  out[i] = g[(e * 15 + i % 15) * p3 + id - e * p3];
 }
 
 // Gauss-Lobatto nodes and weights (Newton on L_{N+1} - L_{N-1} from Chebyshev
@@ -991,7 +894,7 @@ __global__ __launch_bounds__(256) void pj_node_kernel(const DgParams *__restrict
   double *out = pj + (e * rec + (int64_t)node * kPjNode) * 25;
   double qv[5], gv[15];
   for (int v = 0; v < 5; ++v) qv[v] = q[i * 5 + v];
-  for (int t = 0; t < 15; ++t) gv[t] = g[i * 15 + t];
+  for (int t = 0; t < 15; ++t) gv[t] = g[(e * 15 + t) * p3 + node];
   for (int d = 0; d < 3; ++d) {
     for (int kk = 0; kk < 5; ++kk) {
       Dual qd[5], gd[15], f[5];
@@ -1171,13 +1074,12 @@ __global__ void fill_zero_kernel(double *__restrict__ x, int64_t n) {
 struct DgContext {
   DgParams host;
   DgParams *dev = nullptr;
-  double *g = nullptr;
+  double *g = nullptr;     // lifted gradient of the state, then the face fluxes (15 per node, 15 per P^2 of an element)
   double *gd = nullptr;    // lifted gradient of a direction (allocated by the first Newton-matrix product)
   double *gb = nullptr;    // interior-penalty flux: broken gradient of the state (15 doubles per node)
   double *gbd = nullptr;   // ... and of a direction (with gd)
   double *met = nullptr;   // curved elements: 10 doubles per node (NULL: Cartesian cubes)
   uint64_t geo_gen = 0;    // bumped by every geometry change: captured graphs keyed on it recapture
-  bool fused_residual = false;  // residual in one kernel (faces evaluated by both sides) instead of split
   int device = 0;          // the HIP device the object was created on
   int64_t n_nodes = 0;
   hipStream_t stream = nullptr;
@@ -1205,84 +1107,88 @@ struct scdg_dg {
 
 namespace scdg {
 
-// The three face launches of the split operator (the direction is a template
-// argument: the flux code indexes arrays by it).
-template <class T>
-hipError_t launch_faces(const DgContext &c, int n_elem, const double *q, const double *v, const double *gd,
-                        const double *gbd, double *out, hipStream_t s) {
-  const int64_t pairs = (int64_t)n_elem * c.host.p * c.host.p;
-  const unsigned fgrid = (unsigned)((pairs + 255) / 256);
-  if (c.host.sipg) {
-    hipLaunchKernelGGL((face_kernel<T, true, 0>), dim3(fgrid), dim3(256), 0, s, c.dev, pairs, q, v, c.g, gd, c.gb,
-                       gbd, out);
-    hipLaunchKernelGGL((face_kernel<T, true, 1>), dim3(fgrid), dim3(256), 0, s, c.dev, pairs, q, v, c.g, gd, c.gb,
-                       gbd, out);
-    hipLaunchKernelGGL((face_kernel<T, true, 2>), dim3(fgrid), dim3(256), 0, s, c.dev, pairs, q, v, c.g, gd, c.gb,
-                       gbd, out);
-  } else {
-    hipLaunchKernelGGL((face_kernel<T, false, 0>), dim3(fgrid), dim3(256), 0, s, c.dev, pairs, q, v, c.g, gd,
-                       nullptr, nullptr, out);
-    hipLaunchKernelGGL((face_kernel<T, false, 1>), dim3(fgrid), dim3(256), 0, s, c.dev, pairs, q, v, c.g, gd,
-                       nullptr, nullptr, out);
-    hipLaunchKernelGGL((face_kernel<T, false, 2>), dim3(fgrid), dim3(256), 0, s, c.dev, pairs, q, v, c.g, gd,
-                       nullptr, nullptr, out);
+// f<PP>() for the object's nodes per direction
+template <class F>
+hipError_t with_points(int p, F &&f) {
+  switch (p) {
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 7: f(std::integral_constant<int, 7>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+// lifted gradients of q (and of the direction v, when given)
+hipError_t launch_lift(const DgContext &c, const double *q, double *g, double *gb, const double *v, double *gd,
+                       double *gbd, hipStream_t s) {
+  const int n_elem = c.host.k_elem * c.host.k_elem * c.host.k_elem;
+  const LiftArgs a{{q, v}, {g, gd}, {gb, gbd}};
+  return with_points(c.host.p, [&](auto pc) {
+    constexpr int PP = decltype(pc)::value;
+    const dim3 grid(n_elem, v ? 2 : 1), block((PP * PP * PP + 63) / 64 * 64);
+    if (c.met) hipLaunchKernelGGL(lift_curved_kernel<PP>, grid, block, 0, s, c.dev, c.met, a);
+    else hipLaunchKernelGGL(lift_kernel<PP>, grid, block, 0, s, c.dev, a);
+  });
+}
+
+// face fluxes, then the volume sums
+template <class T>
+hipError_t launch_operator(const DgContext &c, DgArgs a, hipStream_t s) {
+  const int n_elem = c.host.k_elem * c.host.k_elem * c.host.k_elem;
+  a.met = c.met;
+  a.face = c.g + 15 * c.n_nodes;
+  a.n_pairs = (int64_t)n_elem * c.host.p * c.host.p;
+  return with_points(c.host.p, [&](auto pc) {
+    constexpr int PP = decltype(pc)::value;
+    const dim3 fgrid((unsigned)((a.n_pairs + 255) / 256), 3), block((PP * PP * PP + 63) / 64 * 64);
+    if (c.met) {
+      hipLaunchKernelGGL((face_flux_kernel<T, PP, kFaceCurved>), fgrid, dim3(256), 0, s, c.dev, a);
+      hipLaunchKernelGGL((volume_kernel<T, PP, true>), dim3(n_elem), block, 0, s, c.dev, a);
+    } else {
+      if (c.host.sipg) hipLaunchKernelGGL((face_flux_kernel<T, PP, kFaceSipg>), fgrid, dim3(256), 0, s, c.dev, a);
+      else hipLaunchKernelGGL((face_flux_kernel<T, PP, kFaceBr1>), fgrid, dim3(256), 0, s, c.dev, a);
+      hipLaunchKernelGGL((volume_kernel<T, PP, false>), dim3(n_elem), block, 0, s, c.dev, a);
+    }
+  });
 }
 
 hipError_t dg_residual_on(scdg_dg *dg, const double *q, const double *q_s, double inv_dt, double *r,
                           hipStream_t s) {
   auto &c = dg->c;
-  const int p3 = c.host.p * c.host.p * c.host.p;
-  const int n_elem = c.host.k_elem * c.host.k_elem * c.host.k_elem;
-  const int threads = ((p3 + 63) / 64) * 64;
-  if (c.met) {
-    hipLaunchKernelGGL(lift_curved_kernel, dim3(n_elem), dim3(threads), sizeof(double) * 10 * p3, s, c.dev, q,
-                       c.met, c.g);
-    hipLaunchKernelGGL(residual_curved_kernel<double>, dim3(n_elem), dim3(threads), sizeof(double) * 15 * p3, s,
-                       c.dev, q, nullptr, c.g, nullptr, c.met, q_s, inv_dt, r);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(lift_kernel, dim3(n_elem), dim3(threads), 0, s, c.dev, q, c.g, c.gb);
-  if (c.fused_residual) {
-    if (c.host.sipg)
-      hipLaunchKernelGGL((residual_kernel<double, true>), dim3(n_elem), dim3(threads), sizeof(double) * 15 * p3, s,
-                         c.dev, q, nullptr, c.g, nullptr, c.gb, nullptr, q_s, inv_dt, r);
-    else
-      hipLaunchKernelGGL((residual_kernel<double, false>), dim3(n_elem), dim3(threads), sizeof(double) * 15 * p3,
-                         s, c.dev, q, nullptr, c.g, nullptr, nullptr, nullptr, q_s, inv_dt, r);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(volume_kernel<double>, dim3(n_elem), dim3(threads), sizeof(double) * 15 * p3, s, c.dev, q,
-                     nullptr, c.g, nullptr, q_s, inv_dt, r);
-  return launch_faces<double>(c, n_elem, q, nullptr, nullptr, nullptr, r, s);
+  const hipError_t e = launch_lift(c, q, c.g, c.gb, nullptr, nullptr, nullptr, s);
+  if (e != hipSuccess) return e;
+  DgArgs a{};
+  a.q = q;
+  a.g = c.g;
+  a.gb = c.gb;
+  a.q_s = q_s;
+  a.r = r;
+  a.inv_dt = inv_dt;
+  return launch_operator<double>(c, a, s);
 }
 
 // out = M inv_dt v + dH/dQ(q) v: the lifted gradients of q and of v (the
 // lifting is linear), then the residual sums on dual numbers (value q,
-// direction v).  c.gd must hold 15 doubles per node.
+// direction v).  gd must hold 15 doubles per node.
 hipError_t dg_jacobian_apply_on(scdg_dg *dg, const double *q, const double *v, double inv_dt, double *out,
                                 hipStream_t s, double *gd, double *gbd) {
   auto &c = dg->c;
-  const int p3 = c.host.p * c.host.p * c.host.p;
-  const int n_elem = c.host.k_elem * c.host.k_elem * c.host.k_elem;
-  const int threads = ((p3 + 63) / 64) * 64;
-  if (c.met) {
-    hipLaunchKernelGGL(lift_curved_kernel, dim3(n_elem), dim3(threads), sizeof(double) * 10 * p3, s, c.dev, q,
-                       c.met, c.g);
-    hipLaunchKernelGGL(lift_curved_kernel, dim3(n_elem), dim3(threads), sizeof(double) * 10 * p3, s, c.dev, v,
-                       c.met, gd);
-    hipLaunchKernelGGL(residual_curved_kernel<Dual>, dim3(n_elem), dim3(threads), sizeof(double) * 15 * p3, s,
-                       c.dev, q, v, c.g, gd, c.met, nullptr, inv_dt, out);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(lift_kernel, dim3(n_elem), dim3(threads), 0, s, c.dev, q, c.g, c.gb);
-  hipLaunchKernelGGL(lift_kernel, dim3(n_elem), dim3(threads), 0, s, c.dev, v, gd, gbd);
-  // volume sums, then the face fluxes once per face (see volume_kernel)
-  hipLaunchKernelGGL(volume_kernel<Dual>, dim3(n_elem), dim3(threads), sizeof(double) * 15 * p3, s, c.dev, q, v,
-                     c.g, gd, nullptr, inv_dt, out);
-  return launch_faces<Dual>(c, n_elem, q, v, gd, gbd, out, s);
-  return hipGetLastError();
+  const hipError_t e = launch_lift(c, q, c.g, c.gb, v, gd, gbd, s);
+  if (e != hipSuccess) return e;
+  DgArgs a{};
+  a.q = q;
+  a.dq = v;
+  a.g = c.g;
+  a.dg = gd;
+  a.gb = c.gb;
+  a.dgb = gbd;
+  a.r = out;
+  a.inv_dt = inv_dt;
+  return launch_operator<Dual>(c, a, s);
 }
 
 int64_t dg_dof_count(const scdg_dg *dg) { return 5 * dg->c.n_nodes; }
@@ -1397,7 +1303,7 @@ scdg_status dg_jacobian_blocks_on(scdg_dg *dg, const JacPlanView &v, const doubl
   hipLaunchKernelGGL(fill_zero_kernel, dim3(fill_grid), dim3(256), 0, s, bb_val, v.nnzb * 25);
   if (hipMemsetAsync(c.jt_flag, 0, sizeof(int32_t), s) != hipSuccess) return fail("flag reset");
   const int threads = ((p3 + 63) / 64) * 64;
-  hipLaunchKernelGGL(lift_kernel, dim3(n_elem), dim3(threads), 0, s, c.dev, q, c.g, nullptr);
+  if (launch_lift(c, q, c.g, nullptr, nullptr, nullptr, nullptr, s) != hipSuccess) return SCDG_ERR_HIP;
   const int64_t n_nodes = (int64_t)n_elem * p3, n_faces = (int64_t)n_elem * 3 * p * p;
   hipLaunchKernelGGL(pj_node_kernel, dim3((unsigned)((n_nodes + 255) / 256)), dim3(256), 0, s, c.dev, q, c.g, c.pj,
                      n_nodes, rec);
@@ -1497,7 +1403,7 @@ scdg_status scdg_dg_create(scdg_dg **out, const scdg_dg_params *prm, void *hip_s
   // allocation; a failure is reported by scdg_dg_jacobian_apply_noalloc)
   (void)scdg::noalloc_resolve(c.device);
   if (hipMalloc(&c.dev, sizeof(scdg::DgParams)) != hipSuccess ||
-      hipMalloc(&c.g, sizeof(double) * 15 * c.n_nodes) != hipSuccess ||
+      hipMalloc(&c.g, sizeof(double) * (15 * c.n_nodes + 15 * (c.n_nodes / P.p))) != hipSuccess ||
       (P.sipg && hipMalloc(&c.gb, sizeof(double) * 15 * c.n_nodes) != hipSuccess) ||
       hipMemcpy(c.dev, &P, sizeof(scdg::DgParams), hipMemcpyHostToDevice) != hipSuccess) {
     if (c.dev) (void)hipFree(c.dev);
@@ -1607,9 +1513,9 @@ scdg_status scdg_dg_set_geometry(scdg_dg *dg, const double *xyz) {
 scdg_status scdg_dg_gradient(scdg_dg *dg, double *g_out) {
   if (!dg || !g_out) return SCDG_ERR_ARG;
   auto &c = dg->c;
-  if (hipMemcpyAsync(g_out, c.g, sizeof(double) * 15 * c.n_nodes, hipMemcpyDeviceToDevice,
-                     c.stream) != hipSuccess)
-    return SCDG_ERR_HIP;
+  hipLaunchKernelGGL(scdg::gradient_export_kernel, dim3((unsigned)((15 * c.n_nodes + 255) / 256)), dim3(256), 0,
+                     c.stream, c.g, c.n_nodes, c.host.p * c.host.p * c.host.p, g_out);
+  if (hipGetLastError() != hipSuccess) return SCDG_ERR_HIP;
   return SCDG_OK;
 }
 
