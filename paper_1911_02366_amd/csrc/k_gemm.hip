@@ -8,13 +8,25 @@
 // once), and the trailing updates of the dense LU of S.
 //
 // Tiling: a workgroup computes a BM x BN tile of one problem; its waves form a
-// WM x WN grid, each owning (BM/WM) x (BN/WN) as a block of 16x16x4 MFMAs.  K advances in steps of 16: the next A and B slabs are loaded
-// into registers (coalesced: consecutive lanes read consecutive addresses)
-// while the current slabs, double-buffered in LDS, feed the matrix cores.  A is
-// stored k-major in LDS so the 16 lanes of one MFMA operand column read
+// WM x WN grid, each owning (BM/WM) x (BN/WN) as a block of 16x16x4 MFMAs.  K
+// advances in steps of 16: the next A and B slabs are loaded into registers
+// (coalesced: consecutive lanes read consecutive addresses) while the current
+// slabs, double-buffered in LDS, feed the matrix cores.  A is stored k-major in
+// LDS so the 16 lanes of one MFMA operand column read
 // consecutive words.  The tile list orders tiles so that one problem's tiles
 // share an XCD (workgroups are dealt to the 8 XCDs round-robin), keeping an
 // element's operands in that XCD's L2.
+//
+// Bound by the matrix cores: an FP64 MFMA keeps a SIMD's vector unit for 64 cycles,
+// so every vector instruction of the loop is time it does not multiply.  The slab
+// loads therefore carry no guard and no address arithmetic (a lane's offset is
+// fixed, the slab's address advances in scalar registers), and the last slab of a
+// K that is no multiple of 16 is a step of its own; guards inside the loop also
+// made the compiler wait for the loads before the products they should overlap.
+// 512 elements of order 5 (K = 320): X 2.39 -> 2.12 ms, T 9.19 -> 8.02 ms in FP64
+// (58.8 TFLOP/s), 1.31 -> 1.13 and 5.26 -> 4.24 ms in FP32; 216 of order 7 (K =
+// 1080): X 21.4 -> 18.6 ms, T 50.0 -> 44.4 ms in FP64 (66.8 TFLOP/s), 11.9 -> 9.3 and
+// 27.7 -> 22.5 ms in FP32 (132 TFLOP/s).
 #include <type_traits>
 
 #include "internal.hpp"
@@ -25,6 +37,22 @@ namespace scdg {
 namespace {
 
 constexpr int BK = 16;
+
+// one element at a 32-bit byte offset from a wave-uniform address (both inside an
+// operand): the address lives in scalar registers, so a slab's advance costs the
+// vector unit nothing
+template <typename T>
+struct Slab {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit Slab(const T *p)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(p), 0, 0xffffffffu, 0x00027000)) {}
+  __device__ __forceinline__ T at(uint32_t off) const {
+    if constexpr (sizeof(T) == 8)
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    else
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+  }
+};
 
 template <typename T, int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDesc *__restrict__ desc,
@@ -67,11 +95,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDe
   const T *__restrict__ b = B + d.b_off;
   T *__restrict__ c = C + d.c_off;
   const int m0 = tm * BM, n0 = tn * BN;
-  if (m0 >= d.m || n0 >= d.n) return;
+  if (m0 >= d.m || n0 >= d.n || d.k < 1) return;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wid = tid >> 6;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wid / WN, wn = wid % WN;
 
   // A slab: lane t reads k = t % 16 of rows t / 16 + step * 16
@@ -79,17 +107,40 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDe
   // B slab: lane t reads column t % BN of k rows t / BN + step * (threads / BN)
   const int b_c = tid % BN, b_k = tid / BN;
 
+  // A lane's 32-bit byte offsets from the slab's first element stay the same for
+  // every slab; the slab's address advances in scalar registers.  Rows past m and
+  // columns past n read the last one's values, which only reach entries that are
+  // never stored; only the last slab of a K that is no multiple of 16 is guarded.
+  uint32_t oa[A_ELEMS], ob[B_ELEMS];
+#pragma unroll
+  for (int u = 0; u < A_ELEMS; ++u)
+    oa[u] = (uint32_t)(min(a_r + u * A_ROWS_PER_STEP, d.m - 1 - m0) * d.lda + a_k) * (uint32_t)sizeof(T);
+#pragma unroll
+  for (int u = 0; u < B_ELEMS; ++u)
+    ob[u] = (uint32_t)((b_k + u * B_ROWS_PER_STEP) * d.ldb + min(b_c, d.n - 1 - n0)) * (uint32_t)sizeof(T);
+  const T *__restrict__ a0 = a + (int64_t)m0 * d.lda;
+  const T *__restrict__ b0 = b + n0;
   T ra[A_ELEMS], rb[B_ELEMS];
   auto load = [&](int k0) {
+    const Slab<T> pa(a0 + k0), pb(b0 + (int64_t)k0 * d.ldb);
+#pragma unroll
+    for (int u = 0; u < A_ELEMS; ++u) ra[u] = pa.at(oa[u]);
+#pragma unroll
+    for (int u = 0; u < B_ELEMS; ++u) rb[u] = pb.at(ob[u]);
+  };
+  auto load_tail = [&](int k0) {               // the last slab, k0 < k < k0 + 16
+    const Slab<T> pa(a0 + k0), pb(b0 + (int64_t)k0 * d.ldb);
+    const bool ka = k0 + a_k < d.k;
 #pragma unroll
     for (int u = 0; u < A_ELEMS; ++u) {
-      const int row = m0 + a_r + u * A_ROWS_PER_STEP, k = k0 + a_k;
-      ra[u] = (row < d.m && k < d.k) ? a[(int64_t)row * d.lda + k] : T(0);
+      const T v = pa.at(ka ? oa[u] : 0);
+      ra[u] = ka ? v : T(0);
     }
 #pragma unroll
     for (int u = 0; u < B_ELEMS; ++u) {
-      const int k = k0 + b_k + u * B_ROWS_PER_STEP, col = n0 + b_c;
-      rb[u] = (k < d.k && col < d.n) ? b[(int64_t)k * d.ldb + col] : T(0);
+      const bool kb = k0 + b_k + u * B_ROWS_PER_STEP < d.k;
+      const T v = pb.at(kb ? ob[u] : 0);
+      rb[u] = kb ? v : T(0);
     }
   };
   auto store = [&](int buf) {
@@ -109,8 +160,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDe
   // wholly in the zero padding of a ragged tile skip their MFMAs (wave-uniform)
   const int tm_valid = min(TM, max(0, (d.m - (m0 + wm * WTM) + 15) / 16));
   const int tn_valid = min(TN, max(0, (d.n - (n0 + wn * WTN) + 15) / 16));
-  const int nk = (d.k + BK - 1) / BK;
-  load(0);
+  const int n_full = d.k / BK, nk = (d.k + BK - 1) / BK;
+  if (n_full > 0) load(0);
+  else load_tail(0);
   store(0);
   __syncthreads();
   // the K loop is compiled twice: without per-block guards for a wave whose
@@ -119,9 +171,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDe
   // reads scheduled around them, and with the guards for the others
   auto kloop = [&](auto full_c) {
     constexpr bool FULL = decltype(full_c)::value;
-    for (int kt = 0; kt < nk; ++kt) {
-      const int buf = kt & 1;
-      if (kt + 1 < nk) load((kt + 1) * BK);
+    auto products = [&](int buf) {
 #pragma unroll
       for (int kk = 0; kk < BK; kk += 4) {
         T af[TM], bf[TN];
@@ -137,9 +187,23 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDe
           for (int j = 0; j < TN; ++j)
             if (FULL || (i < tm_valid && j < tn_valid)) acc[i][j] = M::mma(af[i], bf[j], acc[i][j]);
       }
-      if (kt + 1 < nk) store(buf ^ 1);
+    };
+    int kt = 0;
+    for (; kt + 1 < n_full; ++kt) {
+      load((kt + 1) * BK);
+      products(kt & 1);
+      store((kt + 1) & 1);
       __syncthreads();
     }
+    if (kt + 1 < nk) {
+      load_tail((kt + 1) * BK);
+      products(kt & 1);
+      store((kt + 1) & 1);
+      __syncthreads();
+      ++kt;
+    }
+    products(kt & 1);
+    __syncthreads();                           // the epilogue stages in the slabs' memory
   };
   if (tm_valid == TM && tn_valid == TN)
     kloop(std::true_type{});
