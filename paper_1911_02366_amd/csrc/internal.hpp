@@ -218,12 +218,20 @@ struct Plan {
   int32_t *d_gj_piv = nullptr;     // [sum n_i] pivot row of each column
   unsigned char *d_gj_flag = nullptr;  // [sum n_i] row already used as a pivot
   void *gj_pbuf = nullptr, *gj_rbuf = nullptr;  // [sum n_i * kGjOuter] each
-  size_t cap_gj = 0;
   GemmDesc *d_gj_desc = nullptr;   // per outer panel, the update GEMMs W += P R
   int32_t *d_gj_tiles = nullptr;
   std::vector<int64_t> gj_desc_off, gj_tile_off;
   std::vector<int32_t> gj_ntiles;
   int gj_cfg = -1;                 // tile configuration the lists were built for
+  // the same with pivots inside 64 x 64 diagonal blocks
+  struct {
+    GemmDesc *d_desc = nullptr;    // per outer panel, the GEMMs left and right of it
+    int32_t *d_tiles = nullptr;
+    std::vector<int64_t> desc_off, tile_off;
+    std::vector<int32_t> ntiles;
+  } gjd;
+  void *gj_blk = nullptr;          // per element D^-1 and the block's rows; row scales
+  int32_t *d_gj_state = nullptr;   // nonzero: those pivots do not hold
 
   // dense S path
   double *s_dense = nullptr;       // [n1 * n1] LU of the row-scaled S
@@ -286,6 +294,8 @@ struct Plan {
 // ---- kernel launchers (implemented in the .hip files) ----
 hipError_t launch_gj_inverse(Plan &p, void *work, void *out, bool fp32);
 hipError_t launch_gj_inverse_blocked(Plan &p, void *work, void *out, bool fp32);
+hipError_t launch_gj_inverse_diagonal(Plan &p, void *out, bool fp32);
+size_t gj_diagonal_words(const Plan &p);   // values of gj_blk
 bool gj_supported(int max_n, bool fp32);
 hipError_t launch_gj_inverse_resident(Plan &p, void *work, void *out, bool fp32);
 bool gj_resident_supported(int max_n, bool fp32);

@@ -22,7 +22,10 @@
 // The first panel reads A_ii directly (no separate copy).  Flops: 2 n^3 per
 // element.  A zero or non-finite pivot is recorded LAPACK-style (info = column
 // + 1) and replaced by 1 so the launch always completes.
+// The other forms in this file: resident panels (n up to 400), and two blocked forms
+// for larger blocks.
 #include <algorithm>
+#include <limits>
 #include <type_traits>
 
 #include "internal.hpp"
@@ -795,7 +798,8 @@ __global__ __launch_bounds__(L::NT) void gj_resident_kernel(const double *__rest
 }
 
 // ---------------------------------------------------------------------------
-// Blocked form for large blocks.  Columns are taken in outer panels of
+// Blocked form for large blocks, pivots over whole columns (the form after this one
+// is tried first).  Columns are taken in outer panels of
 // kOuter; inside an outer panel, inner panels of NB columns are eliminated
 // by gj_panel_kernel, which updates only the outer panel's other columns.
 // The rest of the matrix then receives the outer panel's transformation at
@@ -929,6 +933,298 @@ __global__ __launch_bounds__(kThreads) void gj_readout_kernel(const T *__restric
   }
 }
 
+// ---------------------------------------------------------------------------
+// Blocked form with pivots inside 64 x 64 diagonal blocks, tried first.  In place,
+// per block of 64 columns, with D the diagonal block, R its rows and o the others:
+//     P_o = -W[o][blk] D^-1,  P_blk = D^-1,
+//     W[i][j] <- (i in blk ? 0 : W[i][j]) + sum_c P[i][c] R[c][j]  outside the block,
+//     W[i][blk] <- P[i].
+// gj_block_kernel inverts D (Gauss-Jordan, largest row-scaled |a| among the block's
+// unused rows) and copies the rows R of the outer panel's other block;
+// gj_apply_kernel forms P for 64 rows a workgroup and updates that other block;
+// after both blocks of an outer panel, gj_rows_kernel moves its rows aside and one
+// batched GEMM updates the columns left and right of it.  No rows move, so the
+// result needs no read-out.
+//   The pivots are safe where no entry of P in a row still to serve as a pivot,
+// measured on rows scaled by powers of two to largest entries in [1, 2), exceeds
+// kBlockGrowth: the multipliers that partial pivoting keeps at 1 (interior blocks
+// of orders 4 to 7 reach 2 to 8 over the whole column, at sixty times the usual
+// time step 22; |A A^-1 - 1| is then 5e-14 against LAPACK's 1e-12).
+// Where one does, or a pivot is zero or not finite, a flag makes the host run the
+// whole-column form above instead.  The scaling only steers the choice; the values
+// are not scaled.
+//   Bound by memory: a block's sweep reads and writes 128 columns, an outer panel's
+// update the whole block.  216 elements of n = 1080 in FP64: block launches 17 x 45,
+// apply launches 17 x 154 us (3.1 TB/s), rows 9 x 105 us, the GEMMs 11.7 ms (5.4 are
+// bound by C at 4.9 TB/s, 7.1 by the products); the inverse 16.9 ms against 35.7
+// in the whole-column form, whose 60 panel launches took 210 us each.  216 elements
+// of orders 3 to 7: 6.1 against 21 ms.
+// ---------------------------------------------------------------------------
+constexpr int kBlk = 64;
+constexpr int kBlkPad = kBlk + 1;
+constexpr double kBlockGrowth = 32.0;
+
+// W = A_ii, and each row's scale: the power of two that brings its largest entry
+// into [1, 2) (1 for a row without a normal largest entry)
+template <typename T>
+__global__ __launch_bounds__(256) void gj_start_kernel(const double *__restrict__ src, T *__restrict__ work,
+                                                       const int32_t *__restrict__ n_arr,
+                                                       const int64_t *__restrict__ off_arr,
+                                                       const int64_t *__restrict__ voff_arr, T *__restrict__ scale,
+                                                       int32_t *__restrict__ info, int32_t *__restrict__ flag) {
+  const int e = blockIdx.x, n = n_arr[e], lane = threadIdx.x & 63;
+  const int64_t off = off_arr[e];
+  if (threadIdx.x == 0 && blockIdx.y == 0) {
+    info[e] = 0;
+    if (e == 0) *flag = 0;
+  }
+  for (int i = blockIdx.y * 4 + (threadIdx.x >> 6); i < n; i += gridDim.y * 4) {
+    const double *__restrict__ a = src + off + (int64_t)i * n;
+    T *__restrict__ w = work + off + (int64_t)i * n;
+    T big = T(0);
+    for (int j = lane; j < n; j += 64) {
+      const T v = (T)a[j];
+      w[j] = v;
+      big = fmax(big, fabs(v));                // a NaN is passed over here and found by the growth check
+    }
+    big = wave_max_dpp(big);
+    if (lane == 0) {
+      const bool ok = isfinite((double)big) && big >= std::numeric_limits<T>::min() * T(4);
+      const int ex = ok ? ilogb(big) : 0;
+      scale[voff_arr[e] + i] = (T)ldexp(1.0, -ex);
+    }
+  }
+}
+
+// D^-1 of the diagonal block at kb (bordered with the identity to 64 columns) and
+// the block's rows in the outer panel's other block.  Four waves hold 16 columns
+// each, a lane one row; one barrier per column.
+template <typename T>
+__global__ __launch_bounds__(256) void gj_block_kernel(const T *__restrict__ work, const int32_t *__restrict__ n_arr,
+                                                       const int64_t *__restrict__ off_arr,
+                                                       const int64_t *__restrict__ voff_arr,
+                                                       const T *__restrict__ scale, T *__restrict__ dinv,
+                                                       T *__restrict__ rblk, int32_t *__restrict__ flag, int kb,
+                                                       int ko) {
+  const int e = blockIdx.x, n = n_arr[e];
+  if (kb >= n) return;
+  const int nb = min(kBlk, n - kb);
+  const T *__restrict__ w = work + off_arr[e];
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ T colv[2][kBlk];
+  __shared__ int piv[kBlk], qinv[kBlk];
+
+  T x[16];
+#pragma unroll
+  for (int t = 0; t < 16; ++t) {
+    const int col = 16 * wid + t;
+    const bool in = lane < nb && col < nb;
+    const T v = w[(int64_t)(kb + (in ? lane : 0)) * n + kb + (in ? col : 0)];
+    x[t] = in ? v : T(lane == col ? 1 : 0);
+  }
+  const T sc = lane < nb ? scale[voff_arr[e] + kb + lane] : T(1);
+  {
+    const int o0 = kb == ko ? ko + kBlk : ko, ow = min(kBlk, n - o0);
+    T *__restrict__ dst = rblk + (int64_t)e * kBlk * kBlk;
+#pragma unroll
+    for (int u = 0; u < kBlk * kBlk / 256; ++u) {
+      const int idx = tid + u * 256, r = idx / kBlk, c = idx % kBlk;
+      const bool in = r < nb && c < ow;
+      const T v = w[(int64_t)(kb + (in ? r : 0)) * n + (in ? o0 + c : 0)];
+      dst[idx] = in ? v : T(0);
+    }
+  }
+
+  bool used = false, bad = false;
+  for (int q = 0; q < 4; ++q) {
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const int c = 16 * q + t, par = t & 1;
+      if (wid == q) colv[par][lane] = x[t];
+      __syncthreads();
+      const T f = colv[par][lane];
+      const T key = pivot_key(f * sc, !used);
+      const T m = wave_max_dpp(key);
+      const unsigned long long b = __ballot(key == m);
+      const int pr = b ? __ffsll((long long)b) - 1 : 0;
+      T d = read_lane(f, pr);
+      if (!(d != T(0)) || !isfinite((double)d)) {
+        bad = true;
+        d = T(1);
+      }
+      const T inv_d = T(1) / d;
+      used = used || lane == pr;
+      if (tid == 0) piv[c] = pr;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const T pv = read_lane(x[j], pr);
+        const bool self = wid == q && j == t;
+        const T sp = self ? inv_d : pv * inv_d;
+        const T old = self ? T(0) : x[j];
+        const T upd = old - f * sp;
+        x[j] = lane == pr ? sp : upd;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < kBlk) qinv[piv[tid] & (kBlk - 1)] = tid;
+  __syncthreads();
+  T *__restrict__ out = dinv + (int64_t)e * kBlk * kBlk + qinv[lane] * kBlk;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) out[piv[16 * wid + j]] = x[j];
+  if (bad && tid == 0) *flag = 1;
+}
+
+// P for 64 rows (16 a wave), and the update of the outer panel's other block.  In
+// the products, K step s takes k = 16 (lane / 16) + s, so that a lane's A values
+// are 16 consecutive entries of a row.
+template <typename T>
+__global__ __launch_bounds__(256, 2) void gj_apply_kernel(T *__restrict__ work, const int32_t *__restrict__ n_arr,
+                                                       const int64_t *__restrict__ off_arr,
+                                                       const int64_t *__restrict__ voff_arr,
+                                                       const T *__restrict__ scale, const T *__restrict__ dinv,
+                                                       const T *__restrict__ rblk, int32_t *__restrict__ flag, int kb,
+                                                       int ko) {
+  using M = Mfma<T>;
+  const int e = blockIdx.y, n = n_arr[e], r0 = blockIdx.x * kBlk;
+  if (kb >= n || r0 >= n) return;
+  const int nb = min(kBlk, n - kb);
+  const int o0 = kb == ko ? ko + kBlk : ko, ow = min(kBlk, n - o0);
+  T *__restrict__ w = work + off_arr[e];
+  const T *__restrict__ rs = scale + voff_arr[e];
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  __shared__ T bs[kBlk * kBlkPad];            // D^-1, then R
+  __shared__ T ps[4][16 * kBlkPad];           // a wave's 16 rows of P
+
+  const bool diag = r0 == kb;
+  const int row0 = r0 + 16 * wid;
+  const T *__restrict__ dv = dinv + (int64_t)e * kBlk * kBlk;
+  const T *__restrict__ rv = rblk + (int64_t)e * kBlk * kBlk;
+  T st[kBlk * kBlk / 256];
+#pragma unroll
+  for (int u = 0; u < kBlk * kBlk / 256; ++u) st[u] = dv[tid + u * 256];
+  T a[16];
+  {
+    const int row = min(row0 + lr, n - 1);
+    const T *__restrict__ src = w + (int64_t)row * n + kb;
+    if (nb == kBlk) {
+#pragma unroll
+      for (int s = 0; s < 16; ++s) a[s] = src[16 * lg + s];
+    } else {
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        const int k = 16 * lg + s;
+        const T v = src[min(k, nb - 1)];
+        a[s] = k < nb ? v : T(0);
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kBlk * kBlk / 256; ++u) {
+    const int idx = tid + u * 256;
+    bs[(idx / kBlk) * kBlkPad + idx % kBlk] = st[u];
+  }
+  __syncthreads();
+  T *pw = ps[wid];
+  if (diag) {
+#pragma unroll 4
+    for (int i = 0; i < 16; ++i) pw[i * kBlkPad + lane] = bs[(16 * wid + i) * kBlkPad + lane];
+  } else {
+    typename M::acc_t acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = M::zero();
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = M::mma(a[s], bs[(16 * lg + s) * kBlkPad + 16 * j + lr], acc[j]);
+      if (s % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // or all 64 operands are read ahead: 256 registers
+    }
+    T big = T(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const T cs = 16 * j + lr < nb ? T(1) / rs[kb + 16 * j + lr] : T(0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = M::row(lane, r);
+        pw[i * kBlkPad + 16 * j + lr] = -acc[j][r];
+        // rows still to serve as pivots; in the others only what is not finite counts
+        const T g = fabs(acc[j][r]) * (r0 > kb ? rs[min(row0 + i, n - 1)] * cs : T(0));
+        big = g != g ? T(INFINITY) : fmax(big, g);
+      }
+    }
+    if (__ballot(big > T(kBlockGrowth)) != 0ull && lane == 0) *flag = 1;
+  }
+  __syncthreads();                             // D^-1 is no longer read
+  if (ow > 0) {
+#pragma unroll
+    for (int u = 0; u < kBlk * kBlk / 256; ++u) st[u] = rv[tid + u * 256];
+  }
+  // entries past the edges read the last row's and column's values and are not stored
+  T *__restrict__ wo = w + (int64_t)row0 * n + o0;
+  typename M::acc_t acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j] = M::zero();
+  if (ow > 0 && row0 < n) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int col = min(16 * j + lr, ow - 1);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const T v = wo[min(M::row(lane, r), n - 1 - row0) * n + col];
+        acc[j][r] = diag ? T(0) : v;
+      }
+    }
+  }
+  // P into the block's columns
+  T *__restrict__ wp = w + (int64_t)row0 * n + kb;
+#pragma unroll 4
+  for (int i = 0; i < 16; ++i)
+    if (row0 + i < n && lane < nb) wp[i * n + lane] = pw[i * kBlkPad + lane];
+  if (ow <= 0) return;
+#pragma unroll
+  for (int u = 0; u < kBlk * kBlk / 256; ++u) {
+    const int idx = tid + u * 256;
+    bs[(idx / kBlk) * kBlkPad + idx % kBlk] = st[u];
+  }
+#pragma unroll
+  for (int s = 0; s < 16; ++s) a[s] = pw[lr * kBlkPad + 16 * lg + s];
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = M::mma(a[s], bs[(16 * lg + s) * kBlkPad + 16 * j + lr], acc[j]);
+    if (s % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int col = 16 * j + lr;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = M::row(lane, r);
+      if (row0 + i < n && col < ow) wo[i * n + col] = acc[j][r];
+    }
+  }
+}
+
+// R[c][j] = W[ko + c][j] and W[ko + c][j] = 0 outside the outer panel
+template <typename T>
+__global__ __launch_bounds__(256) void gj_rows_kernel(T *__restrict__ work, const int32_t *__restrict__ n_arr,
+                                                      const int64_t *__restrict__ off_arr,
+                                                      const int64_t *__restrict__ voff_arr, T *__restrict__ rbuf,
+                                                      int ko) {
+  const int e = blockIdx.x, n = n_arr[e], c = blockIdx.y * 4 + (threadIdx.x >> 6);
+  const int nbo = min(kOuter, n - ko);
+  if (c >= nbo) return;
+  T *__restrict__ src = work + off_arr[e] + (int64_t)(ko + c) * n;
+  T *__restrict__ dst = rbuf + voff_arr[e] * kOuter + (int64_t)c * n;
+  for (int j = threadIdx.x & 63; j < n; j += 64)
+    if (j < ko || j >= ko + nbo) {
+      dst[j] = src[j];
+      src[j] = T(0);
+    }
+}
+
 template <class L>
 hipError_t gj_launch(Plan &p, typename L::T *work, typename L::T *out) {
   const size_t lds = L::lds_bytes(p.max_ni);
@@ -1008,6 +1304,34 @@ hipError_t gj_blocked_dispatch(Plan &p, T *work, T *out) {
   return gj_blocked_run<GjWide<T, 8, false>>(p, work, out);
 }
 
+// the form with pivots inside 64 x 64 blocks, in place in out; p.gj_state[0] tells
+// afterwards whether it holds
+template <typename T>
+hipError_t gj_diagonal_run(Plan &p, T *out) {
+  T *dinv = static_cast<T *>(p.gj_blk), *rblk = dinv + (int64_t)p.n_elem * kBlk * kBlk;
+  T *scale = rblk + (int64_t)p.n_elem * kBlk * kBlk, *rbuf = static_cast<T *>(p.gj_rbuf);
+  hipLaunchKernelGGL((gj_start_kernel<T>), dim3(p.n_elem, 16), dim3(256), 0, p.stream, p.aii, out, p.d_inv_n,
+                     p.d_inv_off, p.d_gj_voff, scale, p.d_info, p.d_gj_state);
+  for (int s = 0; s * kOuter < p.max_ni; ++s) {
+    const int ko = s * kOuter;
+    for (int kb = ko; kb < std::min(p.max_ni, ko + kOuter); kb += kBlk) {
+      hipLaunchKernelGGL((gj_block_kernel<T>), dim3(p.n_elem), dim3(256), 0, p.stream, out, p.d_inv_n, p.d_inv_off,
+                         p.d_gj_voff, scale, dinv, rblk, p.d_gj_state, kb, ko);
+      hipLaunchKernelGGL((gj_apply_kernel<T>), dim3((p.max_ni + kBlk - 1) / kBlk, p.n_elem), dim3(256), 0, p.stream,
+                         out, p.d_inv_n, p.d_inv_off, p.d_gj_voff, scale, dinv, rblk, p.d_gj_state, kb, ko);
+    }
+    if (p.gjd.ntiles[s] > 0) {
+      hipLaunchKernelGGL((gj_rows_kernel<T>), dim3(p.n_elem, kOuter / 4), dim3(256), 0, p.stream, out, p.d_inv_n,
+                         p.d_inv_off, p.d_gj_voff, rbuf, ko);
+      const hipError_t err =
+          launch_gemm_batched(kGemm64x64, p.gjd.d_desc + p.gjd.desc_off[s], p.gjd.d_tiles + 3 * p.gjd.tile_off[s],
+                              p.gjd.ntiles[s], out, rbuf, out, 1.0, 1.0, sizeof(T) == 4, p.stream);
+      if (err != hipSuccess) return err;
+    }
+  }
+  return hipGetLastError();
+}
+
 template <class L>
 hipError_t gj_res_launch(Plan &p, typename L::T *work, typename L::T *out) {
   const size_t lds = L::lds_bytes(p.max_ni);
@@ -1059,6 +1383,13 @@ hipError_t launch_gj_inverse(Plan &p, void *work, void *out, bool fp32) {
   if (fp32) return gj_dispatch<float>(p, static_cast<float *>(work), static_cast<float *>(out));
   return gj_dispatch<double>(p, static_cast<double *>(work), static_cast<double *>(out));
 }
+
+hipError_t launch_gj_inverse_diagonal(Plan &p, void *out, bool fp32) {
+  return fp32 ? gj_diagonal_run<float>(p, static_cast<float *>(out))
+              : gj_diagonal_run<double>(p, static_cast<double *>(out));
+}
+
+size_t gj_diagonal_words(const Plan &p) { return (size_t)p.n_elem * 2 * kBlk * kBlk + (size_t)p.sum_ni; }
 
 hipError_t launch_gj_inverse_blocked(Plan &p, void *work, void *out, bool fp32) {
   if (fp32) return gj_blocked_dispatch<float>(p, static_cast<float *>(work), static_cast<float *>(out));
