@@ -13,6 +13,8 @@ namespace scdg {
 
 constexpr int kNvar = 5;
 constexpr int kMaxOrder = 7;
+constexpr int kNewtonSegment = 6;    // Arnoldi steps in one captured piece of a restart cycle
+constexpr int kNewtonPieces = 3 + (63 + kNewtonSegment - 1) / kNewtonSegment;   // restart lengths up to 63
 constexpr int kGjOuter = 128;        // outer panel width of the blocked Gauss-Jordan inverse
 constexpr int kDensePanel = 64;       // panel width of the dense LU of S
 constexpr int kKrylovBlocks = 256;    // workgroups (partial sums per value) of the Gram-Schmidt launches
@@ -281,8 +283,10 @@ struct Plan {
   double *nw_r = nullptr;      // [n_dof] nonlinear residual R(Q)
   double *nw_dq = nullptr;     // [n_dof] minus the Newton increment
   double *nw_stat = nullptr;   // [8] norms, see newton_gmres_setup_kernel
-  hipGraph_t nw_graph[3] = {};        // 0: right-hand side and GMRES set-up, 1: one restart
-  hipGraphExec_t nw_exec[3] = {};     //    cycle, 2: back-substitution, update and residual
+  // 0: right-hand side and GMRES set-up, 1: end of a restart cycle, 2: back-substitution,
+  // update and residual, 3 + i: Arnoldi steps i kNewtonSegment and on of a cycle
+  hipGraph_t nw_graph[kNewtonPieces] = {};
+  hipGraphExec_t nw_exec[kNewtonPieces] = {};
   NewtonKey nw_key{};
 
   // phase timing (events recorded asynchronously, summed on query)

@@ -564,7 +564,7 @@ scdg_status gmres(Plan &p, const double *bs, double *x, const double *x0, const 
 // ---- one Newton iteration of the implicit step, captured as a graph ----
 
 void drop_newton_graph(Plan &p) {
-  for (int i = 0; i < 3; ++i) {
+  for (int i = 0; i < kNewtonPieces; ++i) {
     if (p.nw_exec[i]) (void)hipGraphExecDestroy(p.nw_exec[i]);
     if (p.nw_graph[i]) (void)hipGraphDestroy(p.nw_graph[i]);
     p.nw_exec[i] = nullptr;
@@ -601,7 +601,7 @@ NewtonKey newton_key(const Plan &p, scdg_dg *dg, const double *q_s, const double
   return k;
 }
 
-// One Newton iteration is enqueued as three pieces, each captured as a graph.
+// One Newton iteration is enqueued in pieces, each captured as a graph.
 // The linear system is solved for the right-hand side R (not -R):
 // x = S^-1 condense(R), nw_dq = backsolve(R, x) = -dQ.
 // Piece 0: on entry nw_r holds R(Q), nw_stat[0] its squared norm and
@@ -618,23 +618,30 @@ scdg_status newton_piece_setup(Plan &p, const NewtonSetup &ns) {
   return SCDG_OK;
 }
 
-// Piece 1: one restart cycle (m Arnoldi steps that stop on the device flag),
-// x += Dinv V y, the true residual, and the set-up of the next cycle; every
-// kernel returns at once once the solve has finished (kr_st[3]).
-scdg_status newton_piece_cycle(Plan &p, const NewtonSetup &ns) {
+// Pieces 3 and on: the Arnoldi steps j0 to j0 + kNewtonSegment - 1 of a restart cycle,
+// which stop on the device flag.
+scdg_status newton_piece_steps(Plan &p, const NewtonSetup &ns, int j0) {
+  scdg_status st = SCDG_OK;
+  p.halt = p.kr_st;
+  for (int j = j0; j < std::min(ns.m, j0 + kNewtonSegment) && st == SCDG_OK; ++j)
+    st = krylov_step(p, j, ns.m, ns.pmode);
+  p.halt = nullptr;
+  return st;
+}
+
+// Piece 1: the end of a restart cycle: x += Dinv V y, the true residual, and the
+// set-up of the next cycle; every kernel returns at once once the solve has finished
+// (kr_st[3]).
+scdg_status newton_piece_cycle_end(Plan &p, const NewtonSetup &ns) {
   const int64_t n = p.n1;
   const int m = ns.m;
   int32_t *st = p.kr_st;
   const int32_t *done = p.kr_st + 3;
   double *rg = p.gm_w;
-  p.halt = st;
-  scdg_status s1 = SCDG_OK;
-  for (int j = 0; j < m && s1 == SCDG_OK; ++j) s1 = krylov_step(p, j, m, ns.pmode);
   p.halt = done;
-  if (s1 == SCDG_OK) {
-    HIP_TRY(launch_krylov_update(p, m, ns.pmode, krylov_state(p), p.gm_h, p.w_qb, done));
-    s1 = schur_apply_impl(p, p.w_qb, rg);
-  }
+  scdg_status s1 = SCDG_OK;
+  HIP_TRY(launch_krylov_update(p, m, ns.pmode, krylov_state(p), p.gm_h, p.w_qb, done));
+  s1 = schur_apply_impl(p, p.w_qb, rg);
   if (s1 == SCDG_OK) {
     HIP_TRY(launch_krylov_residual(p.w_bs, rg, n, krylov_norm_part(p), p.stream, done));
     HIP_TRY(launch_newton_gmres_restart(krylov_norm_part(p), m, p.kr_g, st, p.kr_dev, p.stream));
@@ -659,14 +666,16 @@ scdg_status newton_graphs(Plan &p, scdg_dg *dg, const double *q_s, double *q, co
   if (p.nw_exec[0] && p.nw_key == key) return SCDG_OK;
   drop_newton_graph(p);
   if (!p.cap_stream) HIP_TRY(hipStreamCreateWithFlags(&p.cap_stream, hipStreamNonBlocking));
-  for (int piece = 0; piece < 3; ++piece) {
+  const int pieces = 3 + (ns.m + kNewtonSegment - 1) / kNewtonSegment;
+  for (int piece = 0; piece < pieces; ++piece) {
     hipStream_t user = p.stream;
     p.stream = p.cap_stream;
     HIP_TRY(hipStreamBeginCapture(p.stream, hipStreamCaptureModeRelaxed));
     p.capturing = true;
     const scdg_status st = piece == 0   ? newton_piece_setup(p, ns)
-                           : piece == 1 ? newton_piece_cycle(p, ns)
-                                        : newton_piece_update(p, dg, q_s, q, ns);
+                           : piece == 1 ? newton_piece_cycle_end(p, ns)
+                           : piece == 2 ? newton_piece_update(p, dg, q_s, q, ns)
+                                        : newton_piece_steps(p, ns, (piece - 3) * kNewtonSegment);
     p.capturing = false;
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(p.stream, &g);
@@ -1800,12 +1809,26 @@ scdg_status scdg_newton_step(scdg_plan *pl, scdg_dg *dg, const double *q_s, doub
   int32_t kst[8];
   while (rn > target && inf.newton < max_newton) {
     HIP_TRY(hipGraphLaunch(p.nw_exec[0], p.stream));
-    // restart cycles until the device flag reports the solve finished
-    for (int c = 0; c < ns.cycles; ++c) {
-      HIP_TRY(hipGraphLaunch(p.nw_exec[1], p.stream));
+    const auto flags = [&]() -> scdg_status {
       HIP_TRY(hipMemcpyAsync(stage + 4, p.kr_st, sizeof(int32_t) * 8, hipMemcpyDeviceToHost, p.stream));
       ST_TRY(sync(p));
       std::memcpy(kst, stage + 4, sizeof(kst));
+      return SCDG_OK;
+    };
+    // restart cycles until the device flag reports the solve finished.  The host looks
+    // at the flag every kNewtonSegment steps: a step past the end of the solve returns
+    // at once in each of its kernels but still costs about 28 us, a look about 15
+    // (512 elements of order 4, three iterations of 11 steps in cycles of 30: 12.5 ms
+    // with 3, 4 or 6 steps a piece, 13.4 with the whole cycle in one)
+    for (int c = 0; c < ns.cycles; ++c) {
+      for (int j = 0; j < ns.m; j += kNewtonSegment) {
+        HIP_TRY(hipGraphLaunch(p.nw_exec[3 + j / kNewtonSegment], p.stream));
+        if (j + kNewtonSegment >= ns.m) break;
+        ST_TRY(flags());
+        if (kst[0]) break;
+      }
+      HIP_TRY(hipGraphLaunch(p.nw_exec[1], p.stream));
+      ST_TRY(flags());
       if (kst[3]) break;
     }
     HIP_TRY(hipGraphLaunch(p.nw_exec[2], p.stream));
