@@ -129,15 +129,94 @@ __global__ __launch_bounds__(kThreads) void gemv_batched_kernel(
 }
 
 // ---------------------------------------------------- BSR product + pull
-// One wave per boundary node g (5 output rows).  Lanes 0..59 cover 12 blocks of
-// row g at a time, lane l taking row (l % 5) of block (l / 5); each lane reads
-// 5 contiguous values, so a wave reads 12 whole blocks (2400 bytes) per step,
-// two steps per loop trip.  The pull of element contributions (lanes 0..4) is
-// loaded before the block loop so its dependent loads overlap it, and the 12
-// partial sums of each output row meet through cross-lane adds (lanes l, l+5,
-// ..., l+55 hold row l % 5): no LDS and no workgroup barrier.  The block
-// values are FP64, or an FP32 copy inside the products of the FP32 forms
-// (accumulation in FP64 either way).
+// U steps of 12 blocks of a block row, n of them from base on: lane l < 60 takes row
+// l % 5 of block l / 5 of each step, five consecutive values, so a wave reads 12 whole
+// blocks a step.  c holds the column index of block base + lane (and from its place
+// among the values), which reach the other lanes by a shuffle.  A lane loads one value
+// of x and reads the other four of its block from LDS (xs, the wave's own U x 64
+// doubles): loaded by every lane, the five values of x took twice as long in the
+// address unit as an FP32 block's.
+template <int U, typename TV, bool TRANS>
+__device__ __forceinline__ double block_row_steps(int64_t base, int n, int c, const int32_t *__restrict__ src_idx,
+                                                  int from, const TV *__restrict__ val,
+                                                  const double *__restrict__ x, double *xs) {
+  constexpr int SW = TRANS ? 5 : 1;
+  const int lane = threadIdx.x & 63, v = lane % 5, bq = min(lane / 5, 11);
+  TV m[U][5];
+  double xv[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int q = min(12 * u + bq, n - 1);     // past the row's end: its last block, not added
+    const int64_t blk = src_idx ? (int64_t)__shfl(from, q) : base + q;
+    const TV *a = val + blk * 25 + (TRANS ? v : v * 5);
+    xv[u] = x[(int64_t)__shfl(c, q) * 5 + v];
+#pragma unroll
+    for (int w = 0; w < 5; ++w) m[u][w] = a[w * SW];
+  }
+  // one wave's LDS operations execute in order; the fences keep the compiler's order
+#pragma unroll
+  for (int u = 0; u < U; ++u) xs[64 * u + lane] = xv[u];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  double s = 0.0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    double d = 0.0;
+#pragma unroll
+    for (int w = 0; w < 5; ++w) d += (double)m[u][w] * xs[64 * u + 5 * bq + w];
+    s += lane < 60 && 12 * u + bq < n ? d : 0.0;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  return s;
+}
+
+// A lane's part of a block row's product, blocks b0 to b1, in trips of 24 blocks (12
+// for a last trip of so few); the column indices are loaded two trips ahead.
+template <typename TV, bool TRANS>
+__device__ __forceinline__ double block_row_part(int64_t b0, int64_t b1, const int32_t *__restrict__ col,
+                                                 const int32_t *__restrict__ src_idx, const TV *__restrict__ val,
+                                                 const double *__restrict__ x, double *xs) {
+  if (b0 >= b1) return 0.0;
+  const int lane = threadIdx.x & 63;
+  const auto place = [&](int64_t base) { return min(base + lane, b1 - 1); };
+  int c0 = col[place(b0)], c1 = col[place(b0 + 24)];
+  int f0 = 0, f1 = 0;
+  if (src_idx) {
+    f0 = src_idx[place(b0)];
+    f1 = src_idx[place(b0 + 24)];
+  }
+  double s = 0.0;
+  for (int64_t base = b0; base < b1; base += 24) {
+    const int c = c0, f = f0;
+    c0 = c1;
+    f0 = f1;
+    if (base + 48 < b1) {
+      c1 = col[place(base + 48)];
+      if (src_idx) f1 = src_idx[place(base + 48)];
+    }
+    const int n = (int)min((int64_t)24, b1 - base);
+    s += n > 12 ? block_row_steps<2, TV, TRANS>(base, n, c, src_idx, f, val, x, xs)
+                : block_row_steps<1, TV, TRANS>(base, n, c, src_idx, f, val, x, xs);
+  }
+  return s;
+}
+
+// Sum over the 12 lanes of each row: row v in lane v (0..4).
+__device__ __forceinline__ double block_row_sum(double s) {
+  // lanes l < 30 add lane l + 30, l < 15 add l + 15, then l < 5 add l + 5 and l + 10
+  s += __shfl_down(s, 30);
+  s += __shfl_down(s, 15);
+  const double s5 = __shfl_down(s, 5), s10 = __shfl_down(s, 10);
+  return s + s5 + s10;
+}
+
+// One wave per boundary node g (5 output rows): the blocks of its row and the pull of
+// the element contributions, 12 at a time over the lanes, so that it adds two loads
+// and not two behind one another for each contribution.  The block values are FP64, or
+// an FP32 copy inside the products of the FP32 forms (accumulation in FP64 either way).
+//   Bound by the blocks' bytes and the address unit: 512 elements of order 4 in FP32
+// (380 MB) 100 -> 83 us (4.6 TB/s), 125 of order 4 in FP64 (182 MB) 36 -> 30 us; the
+// pull alone, 512 elements of order 5, 35 -> 24 us.  Longer trips (36 or 48 blocks)
+// read a row's last block again for its missing places and took 4 and 12 us more.
 template <typename TV, bool TRANS>
 __global__ __launch_bounds__(kThreads) void bsr_pull_kernel_impl(
     int64_t n_bnodes, double c0, const double *__restrict__ src0, const int32_t *__restrict__ map0,
@@ -146,69 +225,31 @@ __global__ __launch_bounds__(kThreads) void bsr_pull_kernel_impl(
     const double *__restrict__ x, double c2, const int32_t *__restrict__ pull_ptr,
     const int32_t *__restrict__ pull_idx, const double *__restrict__ t, double *__restrict__ out,
     const int32_t *__restrict__ halt) {
+  __shared__ double xs[kThreads / 64][2 * 64];
   if (halt && *halt) return;
   const int lane = threadIdx.x & 63;
-  const int64_t g = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  const int64_t g = (int64_t)blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (g >= n_bnodes) return;   // whole waves leave together: no barrier below
+  // the element contributions: lane 5 q + v takes value v of the q-th, 12 at a time
   double p = 0.0, o0 = 0.0;
-  if (lane < 5) {
+  if (c2 != 0.0) {
+    const int q0 = pull_ptr[g], q1 = pull_ptr[g + 1];
+    for (int q = q0 + lane / 5; q < q1 && lane < 60; q += 12) p += t[5 * (int64_t)pull_idx[q] + lane % 5];
+  }
+  if (c0 != 0.0 && lane < 5) {
     const int64_t j = 5 * g + lane;
-    if (c2 != 0.0)
-      for (int q = pull_ptr[g]; q < pull_ptr[g + 1]; ++q) p += t[5 * (int64_t)pull_idx[q] + lane];
-    if (c0 != 0.0) o0 = src0[map0 ? map0[j] : j];
+    o0 = src0[map0 ? map0[j] : j];
   }
   double s = 0.0;
-  const int v = lane % 5, bq = lane / 5;
-  // row v of a stored block, or of its transpose (column v)
-  constexpr int SW = TRANS ? 5 : 1;
-  const int ro = TRANS ? v : v * 5;
-  if (c1 != 0.0 && lane < 60) {
-    const int64_t b0 = rowptr[g], b1 = rowptr[g + 1];
-    double s2 = 0.0;
-    int64_t blk = b0 + bq;
-    for (; blk + 12 < b1; blk += 24) {
-      const int64_t va = src_idx ? (int64_t)src_idx[blk] : blk;
-      const int64_t vb = src_idx ? (int64_t)src_idx[blk + 12] : blk + 12;
-      const TV *ra = val + va * 25 + ro, *rb = val + vb * 25 + ro;
-      const double *xa = x + (int64_t)col[blk] * 5, *xb = x + (int64_t)col[blk + 12] * 5;
-      double ma[5], mb[5], ya[5], yb[5];
-#pragma unroll
-      for (int w = 0; w < 5; ++w) {
-        ma[w] = (double)ra[w * SW];
-        mb[w] = (double)rb[w * SW];
-        ya[w] = xa[w];
-        yb[w] = xb[w];
-      }
-#pragma unroll
-      for (int w = 0; w < 5; ++w) {
-        s += ma[w] * ya[w];
-        s2 += mb[w] * yb[w];
-      }
-    }
-    if (blk < b1) {
-      const int64_t va = src_idx ? (int64_t)src_idx[blk] : blk;
-      const TV *ra = val + va * 25 + ro;
-      const double *xa = x + (int64_t)col[blk] * 5;
-#pragma unroll
-      for (int w = 0; w < 5; ++w) s += (double)ra[w * SW] * xa[w];
-    }
-    s += s2;
-  }
-  // row sums: lanes l < 30 add lane l + 30, l < 15 add l + 15, then l < 5 add l + 5 and l + 10
-  s += __shfl_down(s, 30);
-  s += __shfl_down(s, 15);
-  const double s5 = __shfl_down(s, 5), s10 = __shfl_down(s, 10);
-  if (lane < 5) {
-    double o = c1 * (s + s5 + s10);
-    if (c0 != 0.0) o += c0 * o0;
-    if (c2 != 0.0) o += c2 * p;
-    out[5 * g + lane] = o;
-  }
+  if (c1 != 0.0) s = c1 * block_row_part<TV, TRANS>(rowptr[g], rowptr[g + 1], col, src_idx, val, x, xs[threadIdx.x >> 6]);
+  s = block_row_sum(s + c2 * p);
+  if (lane < 5) out[5 * g + lane] = c0 != 0.0 ? s + c0 * o0 : s;
 }
 
-// y[5 g + v] = sum over the BSR blocks of row g of (block x), one wave per
-// boundary node g, laid out as in bsr_pull_kernel (12 blocks per step, two
-// steps per trip, cross-lane row sums).
+// y[5 g + v] = sum over the BSR blocks of row g of (block x), one wave per boundary
+// node g, lanes as in block_row_steps, every lane loading the whole of its x: beside
+// the element blocks' stream (schur_gemv_rem_kernel) the product of 512 elements of
+// order 5 takes 921 us with it and 935 with block_row_part, 475 and 498 in FP32.
 template <typename TV>
 __device__ __forceinline__ void bsr_rows_wave(int64_t g, const int64_t *__restrict__ rowptr,
                                               const int32_t *__restrict__ col, const TV *__restrict__ val,
@@ -245,10 +286,8 @@ __device__ __forceinline__ void bsr_rows_wave(int64_t g, const int64_t *__restri
     }
     s += s2;
   }
-  s += __shfl_down(s, 30);
-  s += __shfl_down(s, 15);
-  const double s5 = __shfl_down(s, 5), s10 = __shfl_down(s, 10);
-  if (lane < 5) y[5 * g + lane] = s + s5 + s10;
+  s = block_row_sum(s);
+  if (lane < 5) y[5 * g + lane] = s;
 }
 
 // The assembled Schur product's two streams in one launch: the element-block
@@ -468,52 +507,21 @@ __global__ void gather_blocks_ld_kernel(const TM *__restrict__ src, const int64_
 }
 
 // y[ybase[r] + v] = sum over the blocks b of block row r of
-// val[b][v][w] x[5 xnode[b] + w]: one wave per block row, lanes as in the
-// BSR product below (12 blocks per step, two steps per trip, cross-lane sums).
+// val[b][v][w] x[5 xnode[b] + w]: one wave per block row.  512 elements of order 4 in
+// FP32: the boundary rows of A_bi 36 -> 32 us, the interior rows of A_ib 20 -> 17 us.
 template <typename TM>
 __global__ __launch_bounds__(kThreads) void bsr5_rows_kernel(
     int64_t n_rows, const int64_t *__restrict__ rowptr, const int32_t *__restrict__ xnode,
     const TM *__restrict__ val, const double *__restrict__ x, const int64_t *__restrict__ ybase,
     double *__restrict__ y, const int32_t *__restrict__ halt) {
+  __shared__ double xs[kThreads / 64][2 * 64];
   if (halt && *halt) return;
   const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  const int64_t r = (int64_t)blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (r >= n_rows) return;   // whole waves leave together
-  const int v = lane % 5, bq = lane / 5;
-  double s = 0.0;
-  if (lane < 60) {
-    const int64_t b0 = rowptr[r], b1 = rowptr[r + 1];
-    double s2 = 0.0;
-    int64_t blk = b0 + bq;
-    for (; blk + 12 < b1; blk += 24) {
-      const TM *ra = val + blk * 25 + v * 5, *rb = val + (blk + 12) * 25 + v * 5;
-      const double *xa = x + (int64_t)xnode[blk] * 5, *xb = x + (int64_t)xnode[blk + 12] * 5;
-      double ma[5], mb[5], ya[5], yb[5];
-#pragma unroll
-      for (int w = 0; w < 5; ++w) {
-        ma[w] = (double)ra[w];
-        mb[w] = (double)rb[w];
-        ya[w] = xa[w];
-        yb[w] = xb[w];
-      }
-#pragma unroll
-      for (int w = 0; w < 5; ++w) {
-        s += ma[w] * ya[w];
-        s2 += mb[w] * yb[w];
-      }
-    }
-    if (blk < b1) {
-      const TM *ra = val + blk * 25 + v * 5;
-      const double *xa = x + (int64_t)xnode[blk] * 5;
-#pragma unroll
-      for (int w = 0; w < 5; ++w) s += (double)ra[w] * xa[w];
-    }
-    s += s2;
-  }
-  s += __shfl_down(s, 30);
-  s += __shfl_down(s, 15);
-  const double s5 = __shfl_down(s, 5), s10 = __shfl_down(s, 10);
-  if (lane < 5) y[ybase[r] + lane] = s + s5 + s10;
+  const double s = block_row_sum(
+      block_row_part<TM, false>(rowptr[r], rowptr[r + 1], xnode, nullptr, val, x, xs[threadIdx.x >> 6]));
+  if (lane < 5) y[ybase[r] + lane] = s;
 }
 
 // ------------------------------------------------------------ utilities
