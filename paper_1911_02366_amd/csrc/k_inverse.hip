@@ -945,14 +945,21 @@ __global__ __launch_bounds__(kThreads) void gj_readout_kernel(const T *__restric
 // after both blocks of an outer panel, gj_rows_kernel moves its rows aside and one
 // batched GEMM updates the columns left and right of it.  No rows move, so the
 // result needs no read-out.
-//   The pivots are safe where no entry of P in a row still to serve as a pivot,
-// measured on rows scaled by powers of two to largest entries in [1, 2), exceeds
-// kBlockGrowth: the multipliers that partial pivoting keeps at 1 (interior blocks
-// of orders 4 to 7 reach 2 to 8 over the whole column, at sixty times the usual
-// time step 22; |A A^-1 - 1| is then 5e-14 against LAPACK's 1e-12).
-// Where one does, or a pivot is zero or not finite, a flag makes the host run the
-// whole-column form above instead.  The scaling only steers the choice; the values
-// are not scaled.
+//   Elimination loses about the digits by which |L||U| exceeds the matrix, so both
+// factors are bounded, on rows scaled by powers of two to largest entries in [1, 2)
+// at the start: the multipliers (the entries of P in a row still to serve as a pivot)
+// by kBlockMultiplier, and the rows of a block, when they come to serve as pivots, by
+// kBlockGrowth in the columns still to come.  The first alone does not do: each
+// block's multipliers may be moderate and the entries still grow by their product
+// from block to block (multipliers of 4 over 17 blocks: 1e10).  A block's rows are
+// read by gj_block_kernel within the outer panel and by gj_rows_kernel right of it,
+// there before the update by the panel itself, one factor of at most 64 multipliers
+// behind.  Partial pivoting keeps the multipliers at 1 and the growth of these
+// matrices at 2 to 6; interior blocks of orders 4 to 7 have multipliers up to 1.8 and
+// growth up to 2.2 at time steps to 2e-2, 6.2 and 6.9 at sixty times the usual step.
+//   Where a bound is exceeded, or a pivot is zero or not finite, a flag makes the host
+// run the whole-column form above instead.  The scaling only steers the choice; the
+// values are not scaled.
 //   Bound by memory: a block's sweep reads and writes 128 columns, an outer panel's
 // update the whole block.  216 elements of n = 1080 in FP64: block launches 17 x 45,
 // apply launches 17 x 154 us (3.1 TB/s), rows 9 x 105 us, the GEMMs 11.7 ms (5.4 are
@@ -962,7 +969,8 @@ __global__ __launch_bounds__(kThreads) void gj_readout_kernel(const T *__restric
 // ---------------------------------------------------------------------------
 constexpr int kBlk = 64;
 constexpr int kBlkPad = kBlk + 1;
-constexpr double kBlockGrowth = 32.0;
+constexpr double kBlockMultiplier = 4.0;
+constexpr double kBlockGrowth = 8.0;
 
 // W = A_ii, and each row's scale: the power of two that brings its largest entry
 // into [1, 2) (1 for a row without a normal largest entry)
@@ -1022,7 +1030,11 @@ __global__ __launch_bounds__(256) void gj_block_kernel(const T *__restrict__ wor
     const T v = w[(int64_t)(kb + (in ? lane : 0)) * n + kb + (in ? col : 0)];
     x[t] = in ? v : T(lane == col ? 1 : 0);
   }
-  const T sc = lane < nb ? scale[voff_arr[e] + kb + lane] : T(1);
+  const T *__restrict__ rs = scale + voff_arr[e] + kb;
+  const T sc = lane < nb ? rs[lane] : T(1);
+  T big = T(0);                                // the block's rows as pivots, row-scaled
+#pragma unroll
+  for (int t = 0; t < 16; ++t) big = fmax(big, lane < nb ? fabs(x[t]) * sc : T(0));
   {
     const int o0 = kb == ko ? ko + kBlk : ko, ow = min(kBlk, n - o0);
     T *__restrict__ dst = rblk + (int64_t)e * kBlk * kBlk;
@@ -1032,10 +1044,12 @@ __global__ __launch_bounds__(256) void gj_block_kernel(const T *__restrict__ wor
       const bool in = r < nb && c < ow;
       const T v = w[(int64_t)(kb + (in ? r : 0)) * n + (in ? o0 + c : 0)];
       dst[idx] = in ? v : T(0);
+      if (o0 > kb) big = fmax(big, in ? fabs(v) * rs[r] : T(0));
     }
   }
 
-  bool used = false, bad = false;
+  // a NaN here is found as a pivot or by the multipliers
+  bool used = false, bad = big > T(kBlockGrowth);
   for (int q = 0; q < 4; ++q) {
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
@@ -1072,7 +1086,7 @@ __global__ __launch_bounds__(256) void gj_block_kernel(const T *__restrict__ wor
   T *__restrict__ out = dinv + (int64_t)e * kBlk * kBlk + qinv[lane] * kBlk;
 #pragma unroll
   for (int j = 0; j < 16; ++j) out[piv[16 * wid + j]] = x[j];
-  if (bad && tid == 0) *flag = 1;
+  if (__ballot(bad) != 0ull && lane == 0) *flag = 1;
 }
 
 // P for 64 rows (16 a wave), and the update of the outer panel's other block.  In
@@ -1153,7 +1167,7 @@ __global__ __launch_bounds__(256, 2) void gj_apply_kernel(T *__restrict__ work, 
         big = g != g ? T(INFINITY) : fmax(big, g);
       }
     }
-    if (__ballot(big > T(kBlockGrowth)) != 0ull && lane == 0) *flag = 1;
+    if (__ballot(big > T(kBlockMultiplier)) != 0ull && lane == 0) *flag = 1;
   }
   __syncthreads();                             // D^-1 is no longer read
   if (ow > 0) {
@@ -1207,22 +1221,28 @@ __global__ __launch_bounds__(256, 2) void gj_apply_kernel(T *__restrict__ work, 
   }
 }
 
-// R[c][j] = W[ko + c][j] and W[ko + c][j] = 0 outside the outer panel
+// R[c][j] = W[ko + c][j] and W[ko + c][j] = 0 outside the outer panel, a wave per row;
+// the row's growth in the columns still to come
 template <typename T>
 __global__ __launch_bounds__(256) void gj_rows_kernel(T *__restrict__ work, const int32_t *__restrict__ n_arr,
                                                       const int64_t *__restrict__ off_arr,
-                                                      const int64_t *__restrict__ voff_arr, T *__restrict__ rbuf,
-                                                      int ko) {
+                                                      const int64_t *__restrict__ voff_arr,
+                                                      const T *__restrict__ scale, T *__restrict__ rbuf,
+                                                      int32_t *__restrict__ flag, int ko) {
   const int e = blockIdx.x, n = n_arr[e], c = blockIdx.y * 4 + (threadIdx.x >> 6);
   const int nbo = min(kOuter, n - ko);
   if (c >= nbo) return;
+  T big = T(0);
   T *__restrict__ src = work + off_arr[e] + (int64_t)(ko + c) * n;
   T *__restrict__ dst = rbuf + voff_arr[e] * kOuter + (int64_t)c * n;
   for (int j = threadIdx.x & 63; j < n; j += 64)
     if (j < ko || j >= ko + nbo) {
-      dst[j] = src[j];
+      const T v = src[j];
+      dst[j] = v;
       src[j] = T(0);
+      if (j > ko) big = fmax(big, fabs(v));
     }
+  if (__ballot(big * scale[voff_arr[e] + ko + c] > T(kBlockGrowth)) != 0ull && (threadIdx.x & 63) == 0) *flag = 1;
 }
 
 template <class L>
@@ -1322,7 +1342,7 @@ hipError_t gj_diagonal_run(Plan &p, T *out) {
     }
     if (p.gjd.ntiles[s] > 0) {
       hipLaunchKernelGGL((gj_rows_kernel<T>), dim3(p.n_elem, kOuter / 4), dim3(256), 0, p.stream, out, p.d_inv_n,
-                         p.d_inv_off, p.d_gj_voff, rbuf, ko);
+                         p.d_inv_off, p.d_gj_voff, scale, rbuf, p.d_gj_state, ko);
       const hipError_t err =
           launch_gemm_batched(kGemm64x64, p.gjd.d_desc + p.gjd.desc_off[s], p.gjd.d_tiles + 3 * p.gjd.tile_off[s],
                               p.gjd.ntiles[s], out, rbuf, out, 1.0, 1.0, sizeof(T) == 4, p.stream);
