@@ -208,6 +208,10 @@ scdg_status scdg_get_schur_mode(const scdg_plan *p, int32_t *mode);
  * reports the form used by the last scdg_factor (0 before). */
 scdg_status scdg_set_inverse_mode(scdg_plan *p, int32_t mode);
 scdg_status scdg_get_inverse_mode(const scdg_plan *p, int32_t *mode_used);
+/* Elements of the last scdg_factor whose pivots were sought over whole columns: all
+ * of them in forms 1 and 3; in form 2 those whose diagonal blocks held no safe pivots.
+ * Synchronizes the stream. */
+scdg_status scdg_inverse_whole_column(scdg_plan *p, int64_t *n_elem);
 /* First singular element (or -1) and its LAPACK-style info (1-based step). */
 scdg_status scdg_factor_info(scdg_plan *p, int64_t *first_bad_elem, int32_t *info);
 

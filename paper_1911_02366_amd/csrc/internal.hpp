@@ -28,6 +28,7 @@ struct GemmDesc {
   // fold map of this problem's C (m/5 x n/5 node blocks: index into the folded
   // blocks' values, -1 for none), added in the epilogue; -1: no fold
   int64_t f_off = -1;
+  int32_t gate = 0;   // index into the flags of launch_gemm_updates
 };
 
 // One tile of a batched GEMV: rows [row0, row0 + rows) of problem `prob`.
@@ -233,7 +234,8 @@ struct Plan {
     std::vector<int32_t> ntiles;
   } gjd;
   void *gj_blk = nullptr;          // per element D^-1 and the block's rows; row scales
-  int32_t *d_gj_state = nullptr;   // nonzero: those pivots do not hold
+  int32_t *d_gj_state = nullptr;   // [2 n_elem + 1] nonzero: the element's pivots do not hold; work on it
+                                   // has ended; and whether there is one
 
   // dense S path
   double *s_dense = nullptr;       // [n1 * n1] LU of the row-scaled S
@@ -312,6 +314,15 @@ hipError_t launch_gemm_batched(int cfg, const GemmDesc *d_desc, const int32_t *d
                                int32_t n_tiles, const void *a, const void *b, void *c, double alpha,
                                double beta, bool fp32, hipStream_t s, const int32_t *fold_map = nullptr,
                                const double *fold_val = nullptr);
+// C += alpha A B per problem, alpha = +-1, on 64x64 tiles; skip: without the problems
+// with skip[desc.gate] set.  The other form only takes those with only[desc.gate] set,
+// and returns at once when *any is zero.
+hipError_t launch_gemm_updates(const GemmDesc *d_desc, const int32_t *d_tiles, int32_t n_tiles, const void *a,
+                               const void *b, void *c, double alpha, bool fp32, hipStream_t s,
+                               const int32_t *skip = nullptr);
+hipError_t launch_gemm_updates_few(const GemmDesc *d_desc, const int32_t *d_tiles, int32_t n_tiles, const void *a,
+                                   const void *b, void *c, double alpha, bool fp32, hipStream_t s, const int32_t *only,
+                                   const int32_t *any);
 
 // y[omap?omap[y_off+r]:y_off+r] = alpha * sum_c M[r,c] x[xmap?xmap[x_off+c]:x_off+c]
 //                                 + beta * y0[y_off + r]

@@ -592,11 +592,9 @@ hipError_t launch_dense_lu(Plan &p) {
   // written once per pair.
   auto update = [&](int which, int kb, int m, int nn) {
     if (m <= 0 || nn <= 0 || err != hipSuccess) return;
-    const int cfg = kGemm64x64;   // n = 7560: 16.6 ms for the solve, 18.7 with 128x128 tiles from 512 rows on
-    int bm, bn;
-    gemm_tile_shape(cfg, &bm, &bn);
-    err = launch_gemm_batched(cfg, p.d_dense_desc + 2 * (kb / (2 * kPanel)) + which, nullptr,
-                              ((m + bm - 1) / bm) * ((nn + bn - 1) / bn), a, a, a, -1.0, 1.0, false, p.stream);
+    // 64x64 tiles: n = 7560 takes 16.6 ms for the solve, 18.7 with 128x128 from 512 rows on
+    err = launch_gemm_updates(p.d_dense_desc + 2 * (kb / (2 * kPanel)) + which, nullptr,
+                              ((m + 63) / 64) * ((nn + 63) / 64), a, a, a, -1.0, false, p.stream);
   };
   auto panel = [&](int kb, double *lbuf, double *prev) {
     const int nbw = std::min(kPanel, n - kb), rest = n - kb - nbw;

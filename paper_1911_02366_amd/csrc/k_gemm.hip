@@ -27,6 +27,7 @@
 // (58.8 TFLOP/s), 1.31 -> 1.13 and 5.26 -> 4.24 ms in FP32; 216 of order 7 (K =
 // 1080): X 21.4 -> 18.6 ms, T 50.0 -> 44.4 ms in FP64 (66.8 TFLOP/s), 11.9 -> 9.3 and
 // 27.7 -> 22.5 ms in FP32 (132 TFLOP/s).
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.hpp"
@@ -54,14 +55,12 @@ struct Slab {
   }
 };
 
+// One tile of C; tile: its place in the tile list (without a list: the tile of the
+// only problem).
 template <typename T, int BM, int BN, int WM, int WN, bool PRE>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDesc *__restrict__ desc,
-                                                                const int32_t *__restrict__ tiles,
-                                                                const T *__restrict__ A,
-                                                                const T *__restrict__ B,
-                                                                T *__restrict__ C, T alpha, T beta,
-                                                                const int32_t *__restrict__ fmap,
-                                                                const double *__restrict__ fval) {
+__device__ __forceinline__ void gemm_tile(const GemmDesc *__restrict__ desc, const int32_t *__restrict__ tiles, int tile,
+                                          const T *__restrict__ A, const T *__restrict__ B, T *__restrict__ C, T alpha,
+                                          T beta, const int32_t *__restrict__ fmap, const double *__restrict__ fval) {
   using M = Mfma<T>;
   constexpr int kThreads = 64 * WM * WN;
   constexpr int PA = BM + 4;             // LDS row strides (padding against bank conflicts)
@@ -80,15 +79,15 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDe
 
   int prob, tm, tn;
   if (tiles != nullptr) {
-    prob = tiles[3 * blockIdx.x];
-    tm = tiles[3 * blockIdx.x + 1];
-    tn = tiles[3 * blockIdx.x + 2];
+    prob = tiles[3 * tile];
+    tm = tiles[3 * tile + 1];
+    tn = tiles[3 * tile + 2];
     if (prob < 0) return;
   } else {
     prob = 0;
     const int tiles_m = (desc[0].m + BM - 1) / BM;
-    tm = blockIdx.x % tiles_m;
-    tn = blockIdx.x / tiles_m;
+    tm = tile % tiles_m;
+    tn = tile / tiles_m;
   }
   const GemmDesc d = desc[prob];
   const T *__restrict__ a = A + d.a_off;
@@ -292,21 +291,63 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDe
   }
 }
 
-template <int BM, int BN, int WM, int WN, bool PRE = false>
+template <typename T, int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_batched_kernel(const GemmDesc *__restrict__ desc,
+                                                                    const int32_t *__restrict__ tiles,
+                                                                    const T *__restrict__ A, const T *__restrict__ B,
+                                                                    T *__restrict__ C, T alpha, T beta,
+                                                                    const int32_t *__restrict__ fmap,
+                                                                    const double *__restrict__ fval) {
+  gemm_tile<T, BM, BN, WM, WN, false>(desc, tiles, blockIdx.x, A, B, C, alpha, beta, fmap, fval);
+}
+
+template <int BM, int BN, int WM, int WN>
 hipError_t launch_cfg(const GemmDesc *d_desc, const int32_t *d_tiles, int32_t n_tiles,
                       const void *a, const void *b, void *c, double alpha, double beta, bool fp32,
                       hipStream_t s, const int32_t *fmap, const double *fval) {
   const dim3 block(64 * WM * WN);
   if (fp32) {
-    hipLaunchKernelGGL((gemm_batched_kernel<float, BM, BN, WM, WN, PRE>), dim3(n_tiles), block, 0, s,
+    hipLaunchKernelGGL((gemm_batched_kernel<float, BM, BN, WM, WN>), dim3(n_tiles), block, 0, s,
                        d_desc, d_tiles, static_cast<const float *>(a), static_cast<const float *>(b),
                        static_cast<float *>(c), (float)alpha, (float)beta, fmap, fval);
   } else {
-    hipLaunchKernelGGL((gemm_batched_kernel<double, BM, BN, WM, WN, PRE>), dim3(n_tiles), block, 0, s,
+    hipLaunchKernelGGL((gemm_batched_kernel<double, BM, BN, WM, WN>), dim3(n_tiles), block, 0, s,
                        d_desc, d_tiles, static_cast<const double *>(a), static_cast<const double *>(b),
                        static_cast<double *>(c), alpha, beta, fmap, fval);
   }
   return hipGetLastError();
+}
+
+// C += alpha A B, a tile a workgroup; skip: not for problems with skip[desc.gate] set
+template <typename T>
+__global__ __launch_bounds__(256) void gemm_update_kernel(const GemmDesc *__restrict__ desc,
+                                                          const int32_t *__restrict__ tiles, const T *__restrict__ A,
+                                                          const T *__restrict__ B, T *__restrict__ C, T alpha,
+                                                          const int32_t *__restrict__ skip) {
+  if (skip != nullptr) {
+    const int prob = tiles[3 * blockIdx.x];
+    if (prob < 0 || skip[desc[prob].gate]) return;
+  }
+  gemm_tile<T, 64, 64, 2, 2, true>(desc, tiles, blockIdx.x, A, B, C, alpha, T(1), nullptr, nullptr);
+}
+
+// The same for the problems with only[desc.gate] set, mostly none (*any zero): a
+// workgroup goes through every gridDim.x-th tile, so that a launch with nothing to do
+// is small (62 000 workgroups that return at once take about 50 us).
+template <typename T>
+__global__ __launch_bounds__(256) void gemm_update_few_kernel(const GemmDesc *__restrict__ desc,
+                                                              const int32_t *__restrict__ tiles, int n_tiles,
+                                                              const T *__restrict__ A, const T *__restrict__ B,
+                                                              T *__restrict__ C, T alpha,
+                                                              const int32_t *__restrict__ only,
+                                                              const int32_t *__restrict__ any) {
+  if (!*any) return;
+  for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+    const int prob = tiles[3 * t];
+    if (prob < 0 || !only[desc[prob].gate]) continue;
+    gemm_tile<T, 64, 64, 2, 2, true>(desc, tiles, t, A, B, C, alpha, T(1), nullptr, nullptr);
+    __syncthreads();                           // the next tile's slabs
+  }
 }
 
 }  // namespace
@@ -328,9 +369,6 @@ hipError_t launch_gemm_batched(int cfg, const GemmDesc *d_desc, const int32_t *d
                                double beta, bool fp32, hipStream_t s, const int32_t *fold_map,
                                const double *fold_val) {
   if (n_tiles <= 0) return hipSuccess;
-  // the updates of a factorisation: few slabs and C read as well, so its loads count
-  if (cfg == kGemm64x64 && beta == 1 && (alpha == 1 || alpha == -1))
-    return launch_cfg<64, 64, 2, 2, true>(d_desc, d_tiles, n_tiles, a, b, c, alpha, beta, fp32, s, fold_map, fold_val);
   switch (cfg) {
     case 1: return launch_cfg<64, 128, 2, 2>(d_desc, d_tiles, n_tiles, a, b, c, alpha, beta, fp32, s, fold_map, fold_val);
     case 2: return launch_cfg<128, 128, 2, 2>(d_desc, d_tiles, n_tiles, a, b, c, alpha, beta, fp32, s, fold_map, fold_val);
@@ -342,6 +380,38 @@ hipError_t launch_gemm_batched(int cfg, const GemmDesc *d_desc, const int32_t *d
     case 8: return launch_cfg<128, 256, 2, 4>(d_desc, d_tiles, n_tiles, a, b, c, alpha, beta, fp32, s, fold_map, fold_val);
     default: return launch_cfg<64, 64, 2, 2>(d_desc, d_tiles, n_tiles, a, b, c, alpha, beta, fp32, s, fold_map, fold_val);
   }
+}
+
+// the updates of a factorisation, C += alpha A B with alpha = +-1: few slabs and C
+// read as well, so its loads count
+hipError_t launch_gemm_updates(const GemmDesc *d_desc, const int32_t *d_tiles, int32_t n_tiles, const void *a,
+                               const void *b, void *c, double alpha, bool fp32, hipStream_t s, const int32_t *skip) {
+  if (n_tiles <= 0) return hipSuccess;
+  if (fp32)
+    hipLaunchKernelGGL(gemm_update_kernel<float>, dim3(n_tiles), dim3(256), 0, s, d_desc, d_tiles,
+                       static_cast<const float *>(a), static_cast<const float *>(b), static_cast<float *>(c),
+                       (float)alpha, skip);
+  else
+    hipLaunchKernelGGL(gemm_update_kernel<double>, dim3(n_tiles), dim3(256), 0, s, d_desc, d_tiles,
+                       static_cast<const double *>(a), static_cast<const double *>(b), static_cast<double *>(c), alpha,
+                       skip);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_updates_few(const GemmDesc *d_desc, const int32_t *d_tiles, int32_t n_tiles, const void *a,
+                                   const void *b, void *c, double alpha, bool fp32, hipStream_t s, const int32_t *only,
+                                   const int32_t *any) {
+  if (n_tiles <= 0) return hipSuccess;
+  const dim3 grid(std::min(n_tiles, 2048));    // a multiple of the 8 XCDs: tiles stay on their XCD
+  if (fp32)
+    hipLaunchKernelGGL(gemm_update_few_kernel<float>, grid, dim3(256), 0, s, d_desc, d_tiles, n_tiles,
+                       static_cast<const float *>(a), static_cast<const float *>(b), static_cast<float *>(c),
+                       (float)alpha, only, any);
+  else
+    hipLaunchKernelGGL(gemm_update_few_kernel<double>, grid, dim3(256), 0, s, d_desc, d_tiles, n_tiles,
+                       static_cast<const double *>(a), static_cast<const double *>(b), static_cast<double *>(c), alpha,
+                       only, any);
+  return hipGetLastError();
 }
 
 }  // namespace scdg

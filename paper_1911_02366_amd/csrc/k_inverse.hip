@@ -814,18 +814,31 @@ __global__ __launch_bounds__(L::NT) void gj_resident_kernel(const double *__rest
 // ---------------------------------------------------------------------------
 constexpr int kOuter = kGjOuter;
 
+// The kernels of this form work on the elements e with redo[e] set (redo null: on all).
 template <typename T>
-__global__ void gj_prepare_kernel(const double *__restrict__ src, T *__restrict__ work, int64_t total,
-                                  unsigned char *__restrict__ flags, int64_t n_rows, int32_t *__restrict__ info,
-                                  int n_elem) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    work[i] = (T)src[i];
-    if (i < n_rows) flags[i] = 0;
-    if (i < n_elem) info[i] = 0;
+__global__ __launch_bounds__(256) void gj_prepare_kernel(const double *__restrict__ src, T *__restrict__ work,
+                                                         const int32_t *__restrict__ n_arr,
+                                                         const int64_t *__restrict__ off_arr,
+                                                         const int64_t *__restrict__ voff_arr,
+                                                         unsigned char *__restrict__ flags,
+                                                         int32_t *__restrict__ info,
+                                                         const int32_t *__restrict__ redo, int32_t *__restrict__ any) {
+  const int e = blockIdx.x;
+  if (redo && !redo[e]) return;
+  if (redo && blockIdx.y == 0 && threadIdx.x == 0) *any = 1;   // every writer stores 1
+  const int n = n_arr[e];
+  const int64_t total = (int64_t)n * n, off = off_arr[e], voff = voff_arr[e];
+  for (int64_t i = blockIdx.y * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.y * blockDim.x) {
+    work[off + i] = (T)src[off + i];
+    if (i < n) flags[voff + i] = 0;
   }
+  if (blockIdx.y == 0 && threadIdx.x == 0) info[e] = 0;
 }
 
+// One outer panel of an element: its inner panels one after another, then, where
+// columns lie outside it, the operands of their update:
+//   P[i][c] = W[i][ko + c];  R[c][j] = W[p_c][j] outside the outer panel (0 inside),
+//   and W[p_c][j] = 0 outside the outer panel.
 template <class L>
 __global__ __launch_bounds__(kThreads) void gj_panel_kernel(typename L::T *__restrict__ work,
                                                             const int32_t *__restrict__ n_arr,
@@ -833,7 +846,10 @@ __global__ __launch_bounds__(kThreads) void gj_panel_kernel(typename L::T *__res
                                                             const int64_t *__restrict__ voff_arr,
                                                             int32_t *__restrict__ piv_all,
                                                             unsigned char *__restrict__ flags_all,
-                                                            int32_t *__restrict__ info, int kb, int ko) {
+                                                            typename L::T *__restrict__ pbuf,
+                                                            typename L::T *__restrict__ rbuf,
+                                                            int32_t *__restrict__ info,
+                                                            const int32_t *__restrict__ redo, int ko) {
   using T = typename L::T;
   constexpr int NB = L::NB, PS = L::PS;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -841,8 +857,8 @@ __global__ __launch_bounds__(kThreads) void gj_panel_kernel(typename L::T *__res
   __shared__ int red_i[2][kWaves];
   const int e = blockIdx.x;
   const int n = n_arr[e];
-  if (kb >= n) return;
-  const int nbw = min(NB, n - kb);
+  if (ko >= n || (redo && !redo[e])) return;
+  const int nbo = min(kOuter, n - ko);
   T *__restrict__ w = work + off_arr[e];
   int *piv = piv_all + voff_arr[e];
   unsigned char *flags = flags_all + voff_arr[e];
@@ -856,45 +872,36 @@ __global__ __launch_bounds__(kThreads) void gj_panel_kernel(typename L::T *__res
     used[u] = i < n ? flags[i] != 0 : true;
   }
   for (int i = tid; i < rp; i += kThreads) sm.inpanel[i] = 0;
-  for (int idx = tid; idx < rp * NB; idx += kThreads) {
-    const int i = idx / NB, c = idx % NB;
-    T v = T(0);
-    if (i < n && c < nbw) v = w[(int64_t)i * n + kb + c];
-    sm.pnl[i * PS + c] = v;
-  }
-  __syncthreads();
   int my_info = 0;
-  gj_eliminate<L>(sm, n, kb, nbw, used, piv, flags, my_info, red_v, red_i);
-  gj_update<L>(sm, nullptr, false, w, n, kb, nbw, piv, ko, min(n, ko + kOuter));
-  for (int idx = tid; idx < rp * NB; idx += kThreads) {
-    const int i = idx / NB, c = idx % NB;
-    if (i < n && c < nbw) w[(int64_t)i * n + kb + c] = sm.pnl[i * PS + c];
+  for (int kb = ko; kb < ko + nbo; kb += NB) {
+    const int nbw = min(NB, ko + nbo - kb);
+    for (int idx = tid; idx < rp * NB; idx += kThreads) {
+      const int i = idx / NB, c = idx % NB;
+      T v = T(0);
+      if (i < n && c < nbw) v = w[(int64_t)i * n + kb + c];
+      sm.pnl[i * PS + c] = v;
+    }
+    __syncthreads();
+    gj_eliminate<L>(sm, n, kb, nbw, used, piv, flags, my_info, red_v, red_i);
+    gj_update<L>(sm, nullptr, false, w, n, kb, nbw, piv, ko, ko + nbo);
+    for (int idx = tid; idx < rp * NB; idx += kThreads) {
+      const int i = idx / NB, c = idx % NB;
+      if (i < n && c < nbw) w[(int64_t)i * n + kb + c] = sm.pnl[i * PS + c];
+    }
+    for (int c = tid; c < nbw; c += kThreads) sm.inpanel[piv[kb + c]] = 0;
+    __syncthreads();
   }
   if (tid == 0 && my_info != 0 && info[e] == 0) info[e] = my_info;
-}
-
-// P[i][c] = W[i][ko + c];  R[c][j] = W[p_c][j] outside the outer panel (0 inside),
-// and W[p_c][j] = 0 outside the outer panel.
-template <typename T>
-__global__ void gj_outer_gather_kernel(T *__restrict__ work, const int32_t *__restrict__ n_arr,
-                                       const int64_t *__restrict__ off_arr, const int64_t *__restrict__ voff_arr,
-                                       const int32_t *__restrict__ piv_all, T *__restrict__ pbuf,
-                                       T *__restrict__ rbuf, int ko) {
-  const int e = blockIdx.x;
-  const int n = n_arr[e];
-  if (ko >= n) return;
-  const int nbo = min(kOuter, n - ko);
-  T *__restrict__ w = work + off_arr[e];
-  const int32_t *piv = piv_all + voff_arr[e] + ko;
+  if (n <= kOuter) return;
   T *__restrict__ pb = pbuf + voff_arr[e] * kOuter;
   T *__restrict__ rb = rbuf + voff_arr[e] * kOuter;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int lane = tid & 63, wave = tid >> 6;
   // panel copy, a wave per row
-  for (int i = wave; i < n; i += waves)
+  for (int i = wave; i < n; i += kWaves)
     for (int c = lane; c < nbo; c += 64) pb[(int64_t)i * kOuter + c] = w[(int64_t)i * n + ko + c];
   // pivot rows, a wave per row (the panel columns themselves are not touched here)
-  for (int c = wave; c < nbo; c += waves) {
-    T *__restrict__ src = w + (int64_t)piv[c] * n;
+  for (int c = wave; c < nbo; c += kWaves) {
+    T *__restrict__ src = w + (int64_t)piv[ko + c] * n;
     T *__restrict__ dst = rb + (int64_t)c * n;
     for (int j = lane; j < n; j += 64) {
       if (j >= ko && j < ko + nbo) {
@@ -913,10 +920,12 @@ __global__ __launch_bounds__(kThreads) void gj_readout_kernel(const T *__restric
                                                               const int32_t *__restrict__ n_arr,
                                                               const int64_t *__restrict__ off_arr,
                                                               const int64_t *__restrict__ voff_arr,
-                                                              const int32_t *__restrict__ piv_all) {
+                                                              const int32_t *__restrict__ piv_all,
+                                                              const int32_t *__restrict__ redo) {
   __shared__ int pv[kRowsPerThread * kThreads];
   __shared__ int qinv[kRowsPerThread * kThreads];
   const int e = blockIdx.x;
+  if (redo && !redo[e]) return;
   const int n = n_arr[e];
   const int32_t *piv = piv_all + voff_arr[e];
   for (int k = threadIdx.x; k < n; k += kThreads) {
@@ -957,9 +966,10 @@ __global__ __launch_bounds__(kThreads) void gj_readout_kernel(const T *__restric
 // behind.  Partial pivoting keeps the multipliers at 1 and the growth of these
 // matrices at 2 to 6; interior blocks of orders 4 to 7 have multipliers up to 1.8 and
 // growth up to 2.2 at time steps to 2e-2, 6.2 and 6.9 at sixty times the usual step.
-//   Where a bound is exceeded, or a pivot is zero or not finite, a flag makes the host
-// run the whole-column form above instead.  The scaling only steers the choice; the
-// values are not scaled.
+//   Where a bound is exceeded, or a pivot is zero or not finite, a flag ends the work
+// on that element, and the whole-column form above, enqueued behind, inverts the
+// elements flagged.  The host does not look: a call returns at once and can be
+// captured.  The scaling only steers the choice; the values are not scaled.
 //   Bound by memory: a block's sweep reads and writes 128 columns, an outer panel's
 // update the whole block.  216 elements of n = 1080 in FP64: block launches 17 x 45,
 // apply launches 17 x 154 us (3.1 TB/s), rows 9 x 105 us, the GEMMs 11.7 ms (5.4 are
@@ -979,12 +989,15 @@ __global__ __launch_bounds__(256) void gj_start_kernel(const double *__restrict_
                                                        const int32_t *__restrict__ n_arr,
                                                        const int64_t *__restrict__ off_arr,
                                                        const int64_t *__restrict__ voff_arr, T *__restrict__ scale,
-                                                       int32_t *__restrict__ info, int32_t *__restrict__ flag) {
+                                                       int32_t *__restrict__ info, int32_t *__restrict__ flag,
+                                                       int32_t *__restrict__ stop) {
   const int e = blockIdx.x, n = n_arr[e], lane = threadIdx.x & 63;
   const int64_t off = off_arr[e];
   if (threadIdx.x == 0 && blockIdx.y == 0) {
     info[e] = 0;
-    if (e == 0) *flag = 0;
+    flag[e] = 0;
+    stop[e] = 0;
+    if (e == 0) stop[gridDim.x] = 0;           // gj_prepare_kernel tells whether a flag was raised
   }
   for (int i = blockIdx.y * 4 + (threadIdx.x >> 6); i < n; i += gridDim.y * 4) {
     const double *__restrict__ a = src + off + (int64_t)i * n;
@@ -1012,10 +1025,18 @@ __global__ __launch_bounds__(256) void gj_block_kernel(const T *__restrict__ wor
                                                        const int64_t *__restrict__ off_arr,
                                                        const int64_t *__restrict__ voff_arr,
                                                        const T *__restrict__ scale, T *__restrict__ dinv,
-                                                       T *__restrict__ rblk, int32_t *__restrict__ flag, int kb,
-                                                       int ko) {
+                                                       T *__restrict__ rblk, int32_t *__restrict__ flag,
+                                                       int32_t *__restrict__ stop, int kb, int ko) {
   const int e = blockIdx.x, n = n_arr[e];
   if (kb >= n) return;
+  // Workgroups of the other kernels raise flag[e] while some of them still have to
+  // read it, so those read stop[e], which is written here alone.  This workgroup
+  // raises flag[e] itself after its barriers.
+  const bool dead = flag[e] != 0;
+  if (dead) {
+    if (threadIdx.x == 0) stop[e] = 1;
+    return;
+  }
   const int nb = min(kBlk, n - kb);
   const T *__restrict__ w = work + off_arr[e];
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1086,7 +1107,7 @@ __global__ __launch_bounds__(256) void gj_block_kernel(const T *__restrict__ wor
   T *__restrict__ out = dinv + (int64_t)e * kBlk * kBlk + qinv[lane] * kBlk;
 #pragma unroll
   for (int j = 0; j < 16; ++j) out[piv[16 * wid + j]] = x[j];
-  if (__ballot(bad) != 0ull && lane == 0) *flag = 1;
+  if (__ballot(bad) != 0ull && lane == 0) flag[e] = 1;
 }
 
 // P for 64 rows (16 a wave), and the update of the outer panel's other block.  In
@@ -1097,11 +1118,11 @@ __global__ __launch_bounds__(256, 2) void gj_apply_kernel(T *__restrict__ work, 
                                                        const int64_t *__restrict__ off_arr,
                                                        const int64_t *__restrict__ voff_arr,
                                                        const T *__restrict__ scale, const T *__restrict__ dinv,
-                                                       const T *__restrict__ rblk, int32_t *__restrict__ flag, int kb,
-                                                       int ko) {
+                                                       const T *__restrict__ rblk, int32_t *__restrict__ flag,
+                                                       const int32_t *__restrict__ stop, int kb, int ko) {
   using M = Mfma<T>;
   const int e = blockIdx.y, n = n_arr[e], r0 = blockIdx.x * kBlk;
-  if (kb >= n || r0 >= n) return;
+  if (kb >= n || r0 >= n || stop[e]) return;
   const int nb = min(kBlk, n - kb);
   const int o0 = kb == ko ? ko + kBlk : ko, ow = min(kBlk, n - o0);
   T *__restrict__ w = work + off_arr[e];
@@ -1167,7 +1188,7 @@ __global__ __launch_bounds__(256, 2) void gj_apply_kernel(T *__restrict__ work, 
         big = g != g ? T(INFINITY) : fmax(big, g);
       }
     }
-    if (__ballot(big > T(kBlockMultiplier)) != 0ull && lane == 0) *flag = 1;
+    if (__ballot(big > T(kBlockMultiplier)) != 0ull && lane == 0) flag[e] = 1;
   }
   __syncthreads();                             // D^-1 is no longer read
   if (ow > 0) {
@@ -1228,10 +1249,11 @@ __global__ __launch_bounds__(256) void gj_rows_kernel(T *__restrict__ work, cons
                                                       const int64_t *__restrict__ off_arr,
                                                       const int64_t *__restrict__ voff_arr,
                                                       const T *__restrict__ scale, T *__restrict__ rbuf,
-                                                      int32_t *__restrict__ flag, int ko) {
+                                                      int32_t *__restrict__ flag, const int32_t *__restrict__ stop,
+                                                      int ko) {
   const int e = blockIdx.x, n = n_arr[e], c = blockIdx.y * 4 + (threadIdx.x >> 6);
   const int nbo = min(kOuter, n - ko);
-  if (c >= nbo) return;
+  if (c >= nbo || stop[e]) return;
   T big = T(0);
   T *__restrict__ src = work + off_arr[e] + (int64_t)(ko + c) * n;
   T *__restrict__ dst = rbuf + voff_arr[e] * kOuter + (int64_t)c * n;
@@ -1242,7 +1264,7 @@ __global__ __launch_bounds__(256) void gj_rows_kernel(T *__restrict__ work, cons
       src[j] = T(0);
       if (j > ko) big = fmax(big, fabs(v));
     }
-  if (__ballot(big * scale[voff_arr[e] + ko + c] > T(kBlockGrowth)) != 0ull && (threadIdx.x & 63) == 0) *flag = 1;
+  if (__ballot(big * scale[voff_arr[e] + ko + c] > T(kBlockGrowth)) != 0ull && (threadIdx.x & 63) == 0) flag[e] = 1;
 }
 
 template <class L>
@@ -1280,26 +1302,25 @@ hipError_t gj_blocked_run(Plan &p, typename L::T *work, typename L::T *out) {
   hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(gj_panel_kernel<L>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (err != hipSuccess) return err;
-  const int64_t total = p.off_ii[p.n_elem];
-  const int64_t grid = std::min<int64_t>((total + 255) / 256, 8192);
-  hipLaunchKernelGGL((gj_prepare_kernel<T>), dim3((unsigned)grid), dim3(256), 0, p.stream, p.aii, work, total,
-                     p.d_gj_flag, p.sum_ni, p.d_info, p.n_elem);
+  const int32_t *redo = p.d_gj_state;
   T *pbuf = static_cast<T *>(p.gj_pbuf), *rbuf = static_cast<T *>(p.gj_rbuf);
+  hipLaunchKernelGGL((gj_prepare_kernel<T>), dim3(p.n_elem, 16), dim3(256), 0, p.stream, p.aii, work, p.d_inv_n,
+                     p.d_inv_off, p.d_gj_voff, p.d_gj_flag, p.d_info, redo,
+                     redo ? p.d_gj_state + 2 * p.n_elem : nullptr);
   for (int s = 0; s * kOuter < p.max_ni; ++s) {
-    const int ko = s * kOuter;
-    for (int kb = ko; kb < std::min(p.max_ni, ko + kOuter); kb += L::NB)
-      hipLaunchKernelGGL((gj_panel_kernel<L>), dim3(p.n_elem), dim3(kThreads), lds, p.stream, work,
-                         p.d_inv_n, p.d_inv_off, p.d_gj_voff, p.d_gj_piv, p.d_gj_flag, p.d_info, kb, ko);
+    hipLaunchKernelGGL((gj_panel_kernel<L>), dim3(p.n_elem), dim3(kThreads), lds, p.stream, work, p.d_inv_n,
+                       p.d_inv_off, p.d_gj_voff, p.d_gj_piv, p.d_gj_flag, pbuf, rbuf, p.d_info, redo, s * kOuter);
     if (p.gj_ntiles[s] > 0) {
-      hipLaunchKernelGGL((gj_outer_gather_kernel<T>), dim3(p.n_elem), dim3(512), 0, p.stream, work,
-                         p.d_inv_n, p.d_inv_off, p.d_gj_voff, p.d_gj_piv, pbuf, rbuf, ko);
-      err = launch_gemm_batched(p.gj_cfg, p.d_gj_desc + p.gj_desc_off[s], p.d_gj_tiles + 3 * p.gj_tile_off[s],
-                                p.gj_ntiles[s], pbuf, rbuf, work, 1.0, 1.0, sizeof(T) == 4, p.stream);
+      const GemmDesc *desc = p.d_gj_desc + p.gj_desc_off[s];
+      const int32_t *tiles = p.d_gj_tiles + 3 * p.gj_tile_off[s];
+      err = redo ? launch_gemm_updates_few(desc, tiles, p.gj_ntiles[s], pbuf, rbuf, work, 1.0, sizeof(T) == 4,
+                                           p.stream, redo, redo + 2 * p.n_elem)
+                 : launch_gemm_updates(desc, tiles, p.gj_ntiles[s], pbuf, rbuf, work, 1.0, sizeof(T) == 4, p.stream);
       if (err != hipSuccess) return err;
     }
   }
   hipLaunchKernelGGL((gj_readout_kernel<T>), dim3(p.n_elem), dim3(kThreads), 0, p.stream, work, out, p.d_inv_n,
-                     p.d_inv_off, p.d_gj_voff, p.d_gj_piv);
+                     p.d_inv_off, p.d_gj_voff, p.d_gj_piv, redo);
   return hipGetLastError();
 }
 
@@ -1324,28 +1345,29 @@ hipError_t gj_blocked_dispatch(Plan &p, T *work, T *out) {
   return gj_blocked_run<GjWide<T, 8, false>>(p, work, out);
 }
 
-// the form with pivots inside 64 x 64 blocks, in place in out; p.gj_state[0] tells
-// afterwards whether it holds
+// the form with pivots inside 64 x 64 blocks, in place in out; p.d_gj_state[e] tells
+// behind it whether element e has to be inverted again
 template <typename T>
 hipError_t gj_diagonal_run(Plan &p, T *out) {
   T *dinv = static_cast<T *>(p.gj_blk), *rblk = dinv + (int64_t)p.n_elem * kBlk * kBlk;
   T *scale = rblk + (int64_t)p.n_elem * kBlk * kBlk, *rbuf = static_cast<T *>(p.gj_rbuf);
+  int32_t *flag = p.d_gj_state, *stop = flag + p.n_elem;
   hipLaunchKernelGGL((gj_start_kernel<T>), dim3(p.n_elem, 16), dim3(256), 0, p.stream, p.aii, out, p.d_inv_n,
-                     p.d_inv_off, p.d_gj_voff, scale, p.d_info, p.d_gj_state);
+                     p.d_inv_off, p.d_gj_voff, scale, p.d_info, flag, stop);
   for (int s = 0; s * kOuter < p.max_ni; ++s) {
     const int ko = s * kOuter;
     for (int kb = ko; kb < std::min(p.max_ni, ko + kOuter); kb += kBlk) {
       hipLaunchKernelGGL((gj_block_kernel<T>), dim3(p.n_elem), dim3(256), 0, p.stream, out, p.d_inv_n, p.d_inv_off,
-                         p.d_gj_voff, scale, dinv, rblk, p.d_gj_state, kb, ko);
+                         p.d_gj_voff, scale, dinv, rblk, flag, stop, kb, ko);
       hipLaunchKernelGGL((gj_apply_kernel<T>), dim3((p.max_ni + kBlk - 1) / kBlk, p.n_elem), dim3(256), 0, p.stream,
-                         out, p.d_inv_n, p.d_inv_off, p.d_gj_voff, scale, dinv, rblk, p.d_gj_state, kb, ko);
+                         out, p.d_inv_n, p.d_inv_off, p.d_gj_voff, scale, dinv, rblk, flag, stop, kb, ko);
     }
     if (p.gjd.ntiles[s] > 0) {
       hipLaunchKernelGGL((gj_rows_kernel<T>), dim3(p.n_elem, kOuter / 4), dim3(256), 0, p.stream, out, p.d_inv_n,
-                         p.d_inv_off, p.d_gj_voff, scale, rbuf, p.d_gj_state, ko);
-      const hipError_t err =
-          launch_gemm_batched(kGemm64x64, p.gjd.d_desc + p.gjd.desc_off[s], p.gjd.d_tiles + 3 * p.gjd.tile_off[s],
-                              p.gjd.ntiles[s], out, rbuf, out, 1.0, 1.0, sizeof(T) == 4, p.stream);
+                         p.d_inv_off, p.d_gj_voff, scale, rbuf, flag, stop, ko);
+      const hipError_t err = launch_gemm_updates(p.gjd.d_desc + p.gjd.desc_off[s],
+                                                 p.gjd.d_tiles + 3 * p.gjd.tile_off[s], p.gjd.ntiles[s], out, rbuf,
+                                                 out, 1.0, sizeof(T) == 4, p.stream, stop);
       if (err != hipSuccess) return err;
     }
   }

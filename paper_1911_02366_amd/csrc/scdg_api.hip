@@ -1300,7 +1300,7 @@ scdg_status prepare_blocked_inverse(Plan &p) {
   const auto fill = [](const Plan &p, int e, int64_t voff, int ko, std::vector<GemmDesc> &out) {
     const int ni = p.ni[e];
     out.push_back(GemmDesc{voff * kGjOuter, voff * kGjOuter, p.off_ii[e], ni, ni, std::min(kGjOuter, ni - ko),
-                           kGjOuter, ni, ni});
+                           kGjOuter, ni, ni, -1, e});
   };
   ST_TRY(outer_panel_lists(p, kGemm64x64, fill, &p.d_gj_desc, &p.d_gj_tiles, p.gj_desc_off, p.gj_tile_off,
                            p.gj_ntiles));
@@ -1323,31 +1323,29 @@ scdg_status prepare_diagonal_inverse(Plan &p) {
     const int ni = p.ni[e], k = std::min(kGjOuter, ni - ko);
     const auto add = [&](int j, int cols) {
       if (cols > 0)
-        out.push_back(GemmDesc{p.off_ii[e] + ko, voff * kGjOuter + j, p.off_ii[e] + j, ni, cols, k, ni, ni, ni});
+        out.push_back(
+            GemmDesc{p.off_ii[e] + ko, voff * kGjOuter + j, p.off_ii[e] + j, ni, cols, k, ni, ni, ni, -1, e});
     };
     add(0, ko);
     add(ko + k, ni - ko - k);
   };
   ST_TRY(outer_panel_lists(p, kGemm64x64, fill, &p.gjd.d_desc, &p.gjd.d_tiles, p.gjd.desc_off, p.gjd.tile_off,
                            p.gjd.ntiles));
-  return dalloc(p, &p.d_gj_state, 1);
+  return dalloc(p, &p.d_gj_state, (size_t)2 * p.n_elem + 1);
 }
 
-// The blocked inverse: pivots inside diagonal blocks, and where they do not hold
-// the whole-column form.  Which of the two is decided by the device's flag, so a
-// stream that is being captured takes the whole-column form at once.
+// The blocked inverse: pivots inside diagonal blocks, then the whole-column form on
+// the elements whose pivots did not hold.  The device's flags decide, so the call
+// does not wait and a stream under capture takes the same way; with every element
+// held, the second form's launches return at once (20 at 1080 rows).
+// Without room for the first form's blocks the second inverts every element.
 scdg_status blocked_inverse(Plan &p) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  HIP_TRY(hipStreamIsCapturing(p.stream, &cap));
-  if (cap == hipStreamCaptureStatusNone) {
-    ST_TRY(prepare_diagonal_inverse(p));
-    HIP_TRY(launch_gj_inverse_diagonal(p, p.ainv, fp32(p)));
-    int32_t *state = reinterpret_cast<int32_t *>(p.h_pinned);
-    HIP_TRY(hipMemcpyAsync(state, p.d_gj_state, sizeof(int32_t), hipMemcpyDeviceToHost, p.stream));
-    ST_TRY(sync(p));
-    if (*state == 0) return SCDG_OK;
-  }
   ST_TRY(prepare_blocked_inverse(p));
+  const scdg_status st = prepare_diagonal_inverse(p);
+  if (st == SCDG_OK)
+    HIP_TRY(launch_gj_inverse_diagonal(p, p.ainv, fp32(p)));
+  else if (st != SCDG_ERR_NOMEM)
+    return st;
   HIP_TRY(launch_gj_inverse_blocked(p, p.ainv_work, p.ainv, fp32(p)));
   return SCDG_OK;
 }
@@ -1429,6 +1427,19 @@ scdg_status scdg_set_inverse_mode(scdg_plan *pl, int32_t mode) {
 scdg_status scdg_get_inverse_mode(const scdg_plan *pl, int32_t *mode_used) {
   if (!pl || !mode_used) return SCDG_ERR_ARG;
   *mode_used = pl->p.inverse_used;
+  return SCDG_OK;
+}
+
+scdg_status scdg_inverse_whole_column(scdg_plan *pl, int64_t *n_elem) {
+  if (!pl || !n_elem) return SCDG_ERR_ARG;
+  Plan &p = pl->p;
+  if (p.state < 2) return SCDG_ERR_STATE;
+  *n_elem = p.n_elem;
+  if (p.inverse_used != 2 || !p.d_gj_state) return SCDG_OK;
+  std::vector<int32_t> h(p.n_elem);
+  HIP_TRY(hipMemcpyAsync(h.data(), p.d_gj_state, sizeof(int32_t) * p.n_elem, hipMemcpyDeviceToHost, p.stream));
+  ST_TRY(sync(p));
+  *n_elem = std::count_if(h.begin(), h.end(), [](int32_t f) { return f != 0; });
   return SCDG_OK;
 }
 

@@ -255,6 +255,12 @@ class Plan:
         self._check(self.lib.scdg_get_inverse_mode(self.handle, C.byref(v)), "scdg_get_inverse_mode")
         return {0: "none", 1: "single", 2: "blocked", 3: "resident"}[v.value]
 
+    def inverse_whole_column(self) -> int:
+        """Elements of the last factor() whose pivots were sought over whole columns."""
+        n = C.c_int64()
+        self._check(self.lib.scdg_inverse_whole_column(self.handle, C.byref(n)), "scdg_inverse_whole_column")
+        return n.value
+
     def enable_timing(self, on: bool = True):
         self._check(self.lib.scdg_enable_timing(self.handle, int(on)), "scdg_enable_timing")
 
