@@ -246,7 +246,7 @@ struct Plan {
   int32_t *dl_state = nullptr;     // [kDensePanel + 1] its row exchanges, and whether they are swaps
   double *dl_x = nullptr;          // [2 n1] work vectors of the triangular solves
   GemmDesc *d_dense_desc = nullptr;  // updates of each pair of panels
-  int32_t *d_dense_info = nullptr;
+  int32_t *d_dense_info = nullptr; // [2] step of the first zero pivot; whether U grew beyond its bound
   bool dense_factored = false;
 
   // work vectors (doubles)
@@ -414,7 +414,7 @@ scdg_status dg_jacobian_blocks_on(scdg_dg *dg, const JacPlanView &v, const doubl
 
 // dense path
 hipError_t launch_dense_assemble(const Plan &p, double *s_dense);
-hipError_t launch_dense_lu(Plan &p);
+hipError_t launch_dense_lu(Plan &p, bool whole);
 hipError_t launch_dense_solve(Plan &p, const double *b, double *x);
 
 }  // namespace scdg

@@ -7,11 +7,16 @@
 // n rows per column, one after another.  Here the pivots of a panel are first
 // sought in its diagonal block alone (one workgroup, in registers), and the
 // rows below then form their multipliers at once; the panel is accepted when
-// every multiplier is at most kMaxMultiplier (threshold pivoting: on the row-
-// scaled S of the flow systems the largest is 1.3), and otherwise refactored
-// with partial pivoting over all its rows:
+// every multiplier is at most kMaxMultiplier, and otherwise refactored with
+// partial pivoting over all its rows:
 //   diagonal block -> L21 and the test -> (whole-panel pivoting if rejected)
 //   -> row exchanges, U12 = L11^-1 A12 -> A22 -= L21 U12 on the matrix cores.
+// Bounded multipliers alone do not bound the entries, which can still grow by
+// their product from panel to panel, so the rows of U of an accepted panel are
+// measured too; above kMaxGrowth S is factored again, from the start, with partial
+// pivoting in every panel (the host reads that flag with the zero-pivot one).
+// The row-scaled S of flow systems has multipliers up to 2.3 and entries of U up
+// to 1.04 at time steps to 1e-2, 4.5 and 1.3 at 0.1.
 // The triangular solves take one launch per 64 x 64 diagonal block.
 // Factor and solve with the steps around them: 75.0 -> 3.6 ms at n = 2240 and
 // 681 -> 19.3 ms at n = 7560, against whole-column pivoting in one workgroup on
@@ -26,8 +31,10 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kPanel = kDensePanel;
 // largest multiplier accepted from pivots chosen inside a panel's diagonal block
-// (2 is the bound of exact scaled pivoting up to the power-of-two scales)
-constexpr double kMaxMultiplier = 8.0;
+// (2 is the bound of exact scaled pivoting up to the power-of-two scales), and
+// largest entry of U beside them, on rows with largest entries in [1/2, 1)
+constexpr double kMaxMultiplier = 4.0;
+constexpr double kMaxGrowth = 4.0;
 
 // remainder blocks of A_bb (those not folded into an element block)
 __global__ void dense_fill_bb_kernel(int64_t n_bnodes, const int64_t *__restrict__ rowptr,
@@ -72,7 +79,8 @@ __global__ void zero_kernel(double *__restrict__ x, int64_t n) {
 // than the others).  A zero or non-finite row keeps its scale.
 __global__ __launch_bounds__(kThreads) void dense_scale_rows_kernel(double *__restrict__ a, int n,
                                                                     double *__restrict__ scale,
-                                                                    int32_t *__restrict__ perm) {
+                                                                    int32_t *__restrict__ perm,
+                                                                    int32_t *__restrict__ info) {
   __shared__ double red[kThreads / 64];
   double *row = a + (int64_t)blockIdx.x * n;
   double m = 0.0;
@@ -86,6 +94,7 @@ __global__ __launch_bounds__(kThreads) void dense_scale_rows_kernel(double *__re
   if (threadIdx.x == 0) {
     scale[blockIdx.x] = f;
     perm[blockIdx.x] = blockIdx.x;
+    if (blockIdx.x == 0) info[0] = info[1] = 0;
   }
 }
 
@@ -264,7 +273,7 @@ __global__ __launch_bounds__(256) void dense_l21_kernel(const double *__restrict
 }
 
 // Step 3, when the diagonal block's own pivots were rejected (otherwise it
-// returns at once): the panel a[kb:n, kb:kb+nbw] with partial pivoting over all
+// returns at once) or are not to be tried (whole): the panel a[kb:n, kb:kb+nbw] with partial pivoting over all
 // its rows, unblocked and in place, in one workgroup; the swaps go to state,
 // the results to blk and lbuf, and the rows of prev (the pair's first panel's
 // lbuf, or null) move with them.
@@ -272,9 +281,9 @@ __global__ __launch_bounds__(1024) void dense_panel_lu_kernel(double *__restrict
                                                               double *__restrict__ blk, double *__restrict__ lbuf,
                                                               double *__restrict__ prev, int32_t *__restrict__ state,
                                                               int32_t *__restrict__ perm,
-                                                              int32_t *__restrict__ info) {
+                                                              int32_t *__restrict__ info, bool whole) {
   constexpr int NT = 1024;
-  if (state[kPanel] == 0) return;
+  if (!whole && state[kPanel] == 0) return;
   __shared__ double red_v[NT / 64];
   __shared__ int red_i[NT / 64];
   __shared__ double pivot_row[kPanel];
@@ -360,6 +369,7 @@ __global__ __launch_bounds__(1024) void dense_panel_lu_kernel(double *__restrict
     const int64_t i = kb + nbw + q / nbw;
     lbuf[i * kPanel + q % nbw] = a[i * n + kb + q % nbw];
   }
+  if (tid == 0) state[kPanel] = 1;             // read by every thread before the first barrier
   __syncthreads();
   if (wid < 2) diagonal_inverses(lu, rd, wid, lane, blk + kPanel * kPanel);
 }
@@ -373,13 +383,14 @@ __global__ __launch_bounds__(1024) void dense_panel_lu_kernel(double *__restrict
 // that they can be exchanged.  Grid: ceil(n / 64) workgroups; the one at the panel writes its
 // diagonal block, one right of it also the rows of L21 that its index names.
 // After step 3 the exchanges are a list of swaps and the panel is in place, else
-// they are a permutation of the panel's rows.
+// they are a permutation of the panel's rows and entries of U above kMaxGrowth
+// raise info[1].
 __global__ __launch_bounds__(256) void dense_u12_kernel(double *__restrict__ a, int n, int kb, int nbw,
                                                         const double *__restrict__ blk,
                                                         const double *__restrict__ lbuf,
                                                         const double *__restrict__ prev,
                                                         const int32_t *__restrict__ state,
-                                                        int32_t *__restrict__ perm) {
+                                                        int32_t *__restrict__ perm, int32_t *__restrict__ info) {
   __shared__ double t[kPanel][kPanel + 2];
   const int tid = threadIdx.x, lane = tid & 63;
   const int j0 = blockIdx.x * 64, j = j0 + 16 * (tid >> 6) + (lane & 15);
@@ -389,8 +400,13 @@ __global__ __launch_bounds__(256) void dense_u12_kernel(double *__restrict__ a, 
     const int src = tid < nbw ? perm[kb + state[tid]] : 0;
     __syncthreads();
     if (tid < nbw) perm[kb + tid] = src;
-    for (int q = tid; q < nbw * nbw; q += 256)
-      a[(int64_t)(kb + q / nbw) * n + kb + q % nbw] = blk[(q / nbw) * kPanel + q % nbw];
+    bool ok = true;
+    for (int q = tid; q < nbw * nbw; q += 256) {
+      const double v = blk[(q / nbw) * kPanel + q % nbw];
+      ok = ok && (q % nbw < q / nbw || fabs(v) <= kMaxGrowth);
+      a[(int64_t)(kb + q / nbw) * n + kb + q % nbw] = v;
+    }
+    if (!ok) info[1] = 1;                            // every writer stores 1
     return;
   }
   if (j0 > kb && !swaps) {
@@ -450,13 +466,18 @@ __global__ __launch_bounds__(256) void dense_u12_kernel(double *__restrict__ a, 
     __syncthreads();
     solve_lower_16(t, x, lane);
   }
+  bool ok = true;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = 16 * i + Mfma<double>::row(lane, r);
-      if (m < nbw && j < n) a[(int64_t)(kb + m) * n + j] = x[i][r];
+      if (m < nbw && j < n) {
+        a[(int64_t)(kb + m) * n + j] = x[i][r];
+        ok = ok && fabs(x[i][r]) <= kMaxGrowth;
+      }
     }
+  if (!ok && !swaps && j0 > kb) info[1] = 1;
 }
 
 __global__ void dense_permute_kernel(const double *__restrict__ b, const double *__restrict__ scale,
@@ -555,7 +576,7 @@ static hipError_t dense_work(Plan &p) {
   if (err == hipSuccess) err = get(&p.dl_x, (size_t)2 * n);
   if (err == hipSuccess) err = get(&p.dl_perm, (size_t)n);
   if (err == hipSuccess) err = get(&p.dl_state, (size_t)kPanel + 1);
-  if (err == hipSuccess) err = get(&p.d_dense_info, (size_t)1);
+  if (err == hipSuccess) err = get(&p.d_dense_info, (size_t)2);
   if (err != hipSuccess) return err;
   // per pair of panels: the first panel's update of the second's columns, and the
   // pair's update of the rest
@@ -578,15 +599,16 @@ static hipError_t dense_work(Plan &p) {
   return hipSuccess;
 }
 
-hipError_t launch_dense_lu(Plan &p) {
+// whole: partial pivoting over all rows in every panel
+hipError_t launch_dense_lu(Plan &p, bool whole) {
   hipError_t err = dense_work(p);
   if (err != hipSuccess) return err;
   err = launch_dense_assemble(p, p.s_dense);
   if (err != hipSuccess) return err;
   const int32_t n = (int32_t)p.n1;
   double *a = p.s_dense;
-  hipLaunchKernelGGL(dense_scale_rows_kernel, dim3(n), dim3(kThreads), 0, p.stream, a, n, p.dl_scale, p.dl_perm);
-  err = hipMemsetAsync(p.d_dense_info, 0, sizeof(int32_t), p.stream);
+  hipLaunchKernelGGL(dense_scale_rows_kernel, dim3(n), dim3(kThreads), 0, p.stream, a, n, p.dl_scale, p.dl_perm,
+                     p.d_dense_info);
   // Panels in pairs: the first's update goes at once only to the second's columns
   // (and with the second's exchanges to its rows), so the rest of S is read and
   // written once per pair.
@@ -599,14 +621,15 @@ hipError_t launch_dense_lu(Plan &p) {
   auto panel = [&](int kb, double *lbuf, double *prev) {
     const int nbw = std::min(kPanel, n - kb), rest = n - kb - nbw;
     if (nbw <= 0 || err != hipSuccess) return;
-    hipLaunchKernelGGL(dense_block_lu_kernel, dim3(1), dim3(256), 0, p.stream, a, n, kb, nbw, p.dl_blk, p.dl_state);
-    if (rest > 0)
+    if (!whole)
+      hipLaunchKernelGGL(dense_block_lu_kernel, dim3(1), dim3(256), 0, p.stream, a, n, kb, nbw, p.dl_blk, p.dl_state);
+    if (!whole && rest > 0)
       hipLaunchKernelGGL(dense_l21_kernel, dim3((rest + 63) / 64), dim3(256), 0, p.stream, a, n, kb, p.dl_blk,
                          lbuf, p.dl_state);
     hipLaunchKernelGGL(dense_panel_lu_kernel, dim3(1), dim3(1024), 0, p.stream, a, n, kb, nbw, p.dl_blk, lbuf, prev,
-                       p.dl_state, p.dl_perm, p.d_dense_info);
+                       p.dl_state, p.dl_perm, p.d_dense_info, whole);
     hipLaunchKernelGGL(dense_u12_kernel, dim3((n + 63) / 64), dim3(256), 0, p.stream, a, n, kb, nbw, p.dl_blk,
-                       lbuf, prev, p.dl_state, p.dl_perm);
+                       lbuf, prev, p.dl_state, p.dl_perm, p.d_dense_info);
     err = hipGetLastError();
   };
   for (int kb = 0; kb < n && err == hipSuccess; kb += 2 * kPanel) {

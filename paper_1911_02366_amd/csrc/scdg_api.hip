@@ -701,17 +701,19 @@ scdg_status newton_graphs(Plan &p, scdg_dg *dg, const double *q_s, double *q, co
 
 scdg_status dense_solve(Plan &p, const double *bs, double *x) {
   if (!p.dense_factored) {
-    const hipError_t e = launch_dense_lu(p);
-    if (e == hipErrorOutOfMemory) {
-      p.last_error = "out of device memory for the dense LU of S";
-      return SCDG_ERR_NOMEM;
+    int32_t info[2] = {0, 1};
+    for (int whole = 0; whole < 2 && info[1] != 0; ++whole) {   // again where entries grew
+      const hipError_t e = launch_dense_lu(p, whole != 0);
+      if (e == hipErrorOutOfMemory) {
+        p.last_error = "out of device memory for the dense LU of S";
+        return SCDG_ERR_NOMEM;
+      }
+      HIP_TRY(e);
+      HIP_TRY(hipMemcpyAsync(info, p.d_dense_info, sizeof(info), hipMemcpyDeviceToHost, p.stream));
+      ST_TRY(sync(p));
     }
-    HIP_TRY(e);
-    int32_t info = 0;
-    HIP_TRY(hipMemcpyAsync(&info, p.d_dense_info, sizeof(int32_t), hipMemcpyDeviceToHost, p.stream));
-    ST_TRY(sync(p));
-    if (info != 0) {
-      p.last_error = "zero pivot in the dense LU of S at step " + std::to_string(info);
+    if (info[0] != 0) {
+      p.last_error = "zero pivot in the dense LU of S at step " + std::to_string(info[0]);
       return SCDG_ERR_SINGULAR;
     }
     p.dense_factored = true;
