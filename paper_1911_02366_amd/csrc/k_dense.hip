@@ -18,9 +18,10 @@
 // The row-scaled S of flow systems has multipliers up to 2.3 and entries of U up
 // to 1.04 at time steps to 1e-2, 4.5 and 1.3 at 0.1.
 // The triangular solves take one launch per 64 x 64 diagonal block.
-// Factor and solve with the steps around them: 75.0 -> 3.6 ms at n = 2240 and
-// 681 -> 19.3 ms at n = 7560, against whole-column pivoting in one workgroup on
-// 32-column panels and two barriers a column in the triangular solves.
+// Factor and solve with the steps around them: 75.0 -> 3.3 ms at n = 2240 and
+// 681 -> 16.6 ms at n = 7560, against whole-column pivoting in one workgroup on
+// 32-column panels and two barriers a column in the triangular solves; with
+// every panel rejected 52 and 617 ms.
 #include "internal.hpp"
 #include "mfma.hpp"
 
@@ -274,7 +275,9 @@ __global__ __launch_bounds__(256) void dense_l21_kernel(const double *__restrict
 
 // Step 3, when the diagonal block's own pivots were rejected (otherwise it
 // returns at once) or are not to be tried (whole): the panel a[kb:n, kb:kb+nbw] with partial pivoting over all
-// its rows, unblocked and in place, in one workgroup; the swaps go to state,
+// its rows, in place, in one workgroup, 32 columns at a time and then their update
+// of the others (every column step reads and writes the columns it updates, a row a
+// thread: 64 columns at once cost twice the memory traffic); the swaps go to state,
 // the results to blk and lbuf, and the rows of prev (the pair's first panel's
 // lbuf, or null) move with them.
 __global__ __launch_bounds__(1024) void dense_panel_lu_kernel(double *__restrict__ a, int n, int kb, int nbw,
@@ -282,8 +285,9 @@ __global__ __launch_bounds__(1024) void dense_panel_lu_kernel(double *__restrict
                                                               double *__restrict__ prev, int32_t *__restrict__ state,
                                                               int32_t *__restrict__ perm,
                                                               int32_t *__restrict__ info, bool whole) {
-  constexpr int NT = 1024;
-  if (!whole && state[kPanel] == 0) return;
+  constexpr int NT = 1024, kSub = kPanel / 2;
+  // info[1]: S is factored again anyway (the row indexes left in state stay below n)
+  if (!whole && (state[kPanel] == 0 || info[1] != 0)) return;
   __shared__ double red_v[NT / 64];
   __shared__ int red_i[NT / 64];
   __shared__ double pivot_row[kPanel];
@@ -291,7 +295,7 @@ __global__ __launch_bounds__(1024) void dense_panel_lu_kernel(double *__restrict
   __shared__ double rd[kPanel];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   for (int c = 0; c < nbw; ++c) {
-    const int k = kb + c;
+    const int k = kb + c, end = c < kSub ? min(nbw, kSub) : nbw;
     double best = -1.0;
     int bi = n;
     for (int i = k + tid; i < n; i += NT) {
@@ -354,7 +358,38 @@ __global__ __launch_bounds__(1024) void dense_panel_lu_kernel(double *__restrict
       double *row = a + (int64_t)i * n;
       const double l = row[k] * inv_d;
       row[k] = l;
-      for (int j = c + 1; j < nbw; ++j) row[kb + j] -= l * pivot_row[j];
+      for (int j = c + 1; j < end; ++j) row[kb + j] -= l * pivot_row[j];
+    }
+    __syncthreads();
+    if (c != kSub - 1 || nbw <= kSub) continue;
+    // the second half's columns: U12 (into the second half of lu) from L11, then the rows below
+    for (int q = tid; q < kSub * kSub; q += NT) lu[q / kSub][q % kSub] = a[(int64_t)(kb + q / kSub) * n + kb + q % kSub];
+    __syncthreads();
+    if (tid < nbw - kSub) {
+      double x[kSub];
+#pragma unroll
+      for (int r = 0; r < kSub; ++r) {
+        double *at = a + (int64_t)(kb + r) * n + kb + kSub + tid;
+        double v = *at;
+#pragma unroll
+        for (int q = 0; q < r; ++q) v -= lu[r][q] * x[q];
+        x[r] = v;
+        *at = v;
+        lu[kSub + r][tid] = v;
+      }
+    }
+    __syncthreads();
+    for (int i = kb + kSub + tid; i < n; i += NT) {
+      double *row = a + (int64_t)i * n + kb;
+      double l[kSub];
+#pragma unroll
+      for (int q = 0; q < kSub; ++q) l[q] = row[q];
+      for (int j = kSub; j < nbw; ++j) {
+        double v = row[j];
+#pragma unroll
+        for (int q = 0; q < kSub; ++q) v -= l[q] * lu[kSub + q][j - kSub];
+        row[j] = v;
+      }
     }
     __syncthreads();
   }
