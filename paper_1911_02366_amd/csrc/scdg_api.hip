@@ -514,6 +514,10 @@ scdg_status gmres_cycles(Plan &p, const double *bs, double *x, double *r, double
     if (done == 0) break;   // no progress possible (breakdown at the first step)
   }
   info.iters += it;
+  if (!std::isfinite(beta)) {   // the loop's own test is not reached: a NaN is not above the target
+    p.last_error = "non-finite GMRES residual";
+    return SCDG_ERR_NONFINITE;
+  }
   if (beta > target) {
     p.last_error = "GMRES did not reach the tolerance";
     return SCDG_ERR_NOCONV;
