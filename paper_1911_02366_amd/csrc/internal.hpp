@@ -73,17 +73,14 @@ struct KrylovKey {
   int m = 0, pmode = -1, smode = 0;
   uint64_t sp_gen = 0;
   bool fp32 = false;
-  const void *sloc = nullptr, *bb_val = nullptr, *gm_v = nullptr;
-  // the matrix-free forms' operands: block-sparse lists, work vector, and the
-  // caller's A_ib / A_bi (their addresses can change with every assemble); the
-  // cycle's own state
-  const void *sp[8] = {};
+  // every buffer of the cycle that can move: the factors and blocks of the three
+  // forms of the products (some are allocated again when the precision changes, the
+  // caller's with every assemble), the basis and the cycle's own state
+  const void *ptr[22] = {};
   bool operator==(const KrylovKey &o) const {
-    for (int i = 0; i < 8; ++i)
-      if (sp[i] != o.sp[i]) return false;
-    return m == o.m && pmode == o.pmode && smode == o.smode && sp_gen == o.sp_gen && fp32 == o.fp32 &&
-           sloc == o.sloc &&
-           bb_val == o.bb_val && gm_v == o.gm_v;
+    for (int i = 0; i < 22; ++i)
+      if (ptr[i] != o.ptr[i]) return false;
+    return m == o.m && pmode == o.pmode && smode == o.smode && sp_gen == o.sp_gen && fp32 == o.fp32;
   }
 };
 

@@ -384,12 +384,13 @@ scdg_status krylov_graph(Plan &p, int m, int pmode) {
   key.m = m;
   key.pmode = pmode;
   key.fp32 = fp32(p);
-  key.sloc = p.sloc;
-  key.bb_val = p.bb_val;
-  key.gm_v = p.gm_v;
   key.smode = p.schur_mode;
-  const void *sp[8] = {p.sp_ib.val, p.sp_ib.d_rowptr, p.sp_bi.val, p.sp_bi.d_rowptr, p.w_z2, p.aib, p.abi, p.kr_H};
-  for (int i = 0; i < 8; ++i) key.sp[i] = sp[i];
+  const void *ptr[22] = {p.ainv,   p.xmat,      p.sloc,           p.aib,       p.abi,
+                         p.abi_lo, p.bb_val,    p.bb_lo,          p.rem_val,   p.rem_lo,
+                         p.w_z2,   p.sp_ib.val, p.sp_ib.d_rowptr, p.sp_bi.val, p.sp_bi.d_rowptr,
+                         p.gm_v,   p.kr_H,      p.kr_cs,          p.kr_sn,     p.kr_g,
+                         p.kr_st,  p.kr_dev};
+  for (int i = 0; i < 22; ++i) key.ptr[i] = ptr[i];
   key.sp_gen = p.sp_gen;
   if (p.kr_exec && p.kr_key == key) return SCDG_OK;
   drop_krylov_graph(p);
