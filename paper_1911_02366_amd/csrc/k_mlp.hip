@@ -47,16 +47,16 @@ __device__ __forceinline__ float bf16_round(float x) {
 __device__ __forceinline__ short bf16_bits(float x) { return (short)(__float_as_uint(x) >> 16); }
 
 // C = op(A) op(B) (+ bias[col]) (tanh) (* (1 - D^2)); op(A) is M x K, op(B) K x N.
-// The operands are rounded to bfloat16 when staged in LDS and multiplied
+// BF: the operands are rounded to bfloat16 when staged in LDS and multiplied
 // by the 16x16x16 bf16 MFMA with FP32 accumulation (products of two bf16
-// values are exact in FP32).
-template <bool TA, bool TB>
-__global__ __launch_bounds__(kThreads) void mlp_gemm_bf16_kernel(int M, int N, int K,
-                                                                 const float *__restrict__ A, int lda,
-                                                                 const float *__restrict__ B, int ldb,
-                                                                 float *__restrict__ C, int ldc,
-                                                                 const float *__restrict__ bias, int epi,
-                                                                 const float *__restrict__ dact, int ldd) {
+// values are exact in FP32); otherwise FP32 operands and the 16x16x4 FP32 MFMA.
+template <bool TA, bool TB, bool BF>
+__global__ __launch_bounds__(kThreads) void mlp_gemm_kernel(int M, int N, int K,
+                                                            const float *__restrict__ A, int lda,
+                                                            const float *__restrict__ B, int ldb,
+                                                            float *__restrict__ C, int ldc,
+                                                            const float *__restrict__ bias, int epi,
+                                                            const float *__restrict__ dact, int ldd) {
   using MF = Mfma<float>;
   __shared__ float as[2][kBK][kTile + 4];
   __shared__ float bs[2][kBK][kTile + 4];
@@ -100,8 +100,8 @@ __global__ __launch_bounds__(kThreads) void mlp_gemm_bf16_kernel(int M, int N, i
   auto store = [&](int buf) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const float va = bf16_round(ra[u]);
-      const float vb = bf16_round(rb[u]);
+      const float va = BF ? bf16_round(ra[u]) : ra[u];
+      const float vb = BF ? bf16_round(rb[u]) : rb[u];
       if (TA)
         as[buf][tid / kTile + 4 * u][tid % kTile] = va;
       else
@@ -126,21 +126,36 @@ __global__ __launch_bounds__(kThreads) void mlp_gemm_bf16_kernel(int M, int N, i
   for (int kt = 0; kt < nk; ++kt) {
     const int buf = kt & 1;
     if (kt + 1 < nk) load((kt + 1) * kBK);
-    // 16x16x16: lane l holds A[l % 16][4 (l / 16) + t] and B[4 (l / 16) + t][l % 16], t = 0..3
-    bf16x4 af[2], bf[2];
+    if constexpr (BF) {
+      // 16x16x16: lane l holds A[l % 16][4 (l / 16) + t] and B[4 (l / 16) + t][l % 16], t = 0..3
+      bf16x4 af[2], bf[2];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int k = 4 * (lane >> 4) + t;
+      for (int t = 0; t < 4; ++t) {
+        const int k = 4 * (lane >> 4) + t;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) af[i][t] = bf16_bits(as[buf][k][wm * 32 + i * 16 + (lane & 15)]);
+        for (int i = 0; i < 2; ++i) af[i][t] = bf16_bits(as[buf][k][wm * 32 + i * 16 + (lane & 15)]);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) bf[j][t] = bf16_bits(bs[buf][k][wn * 32 + j * 16 + (lane & 15)]);
+        for (int j = 0; j < 2; ++j) bf[j][t] = bf16_bits(bs[buf][k][wn * 32 + j * 16 + (lane & 15)]);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af[i], bf[j], acc[i][j], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < kBK; kk += 4) {
+        float af[2], bf[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) af[i] = as[buf][kk + (lane >> 4)][wm * 32 + i * 16 + (lane & 15)];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) bf[j] = bs[buf][kk + (lane >> 4)][wn * 32 + j * 16 + (lane & 15)];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = MF::mma(af[i], bf[j], acc[i][j]);
+      }
     }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af[i], bf[j], acc[i][j], 0, 0, 0);
     if (kt + 1 < nk) store(buf ^ 1);
     __syncthreads();
   }
@@ -450,30 +465,49 @@ hipError_t grad_f32(int M, int N, int K, const float *A, int lda, const float *B
   return hipGetLastError();
 }
 
-hipError_t gemm_bf16(bool ta, bool tb, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
-                     float *C, int ldc, const float *bias, int epi, const float *dact, int ldd, hipStream_t s) {
+template <bool BF>
+hipError_t gemm_staged(bool ta, bool tb, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
+                       float *C, int ldc, const float *bias, int epi, const float *dact, int ldd, hipStream_t s) {
   const dim3 grid((M + kTile - 1) / kTile, (N + kTile - 1) / kTile);
   if (ta)
-    hipLaunchKernelGGL((mlp_gemm_bf16_kernel<true, false>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C,
+    hipLaunchKernelGGL((mlp_gemm_kernel<true, false, BF>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C,
                        ldc, bias, epi, dact, ldd);
   else if (tb)
-    hipLaunchKernelGGL((mlp_gemm_bf16_kernel<false, true>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C,
+    hipLaunchKernelGGL((mlp_gemm_kernel<false, true, BF>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C,
                        ldc, bias, epi, dact, ldd);
   else
-    hipLaunchKernelGGL((mlp_gemm_bf16_kernel<false, false>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C,
+    hipLaunchKernelGGL((mlp_gemm_kernel<false, false, BF>), grid, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C,
                        ldc, bias, epi, dact, ldd);
   return hipGetLastError();
 }
 
+// Tiles of 64 x 64 staged in LDS for the products that fill the card with them, where
+// the operands' reuse counts and not the latency (square networks, w wide):
+//   layers, K in one wave's order either way, from 1024 tiles and K = 768 on: w = 1024,
+// 4096 rows 124 against 128 us, 2048 and 16384 rows 1707 against 1796; below,
+// w = 768, 4096 rows (768 tiles) 75.5 against 72.7, and at K = 512 with 2048 tiles 129
+// against 116;
+//   gradients from 512 tiles on: dZ of w = 256, 8192 rows 18.5 against 21.1, of w = 1024,
+// 2048 rows 54 against 59, dW of w = 2048 (1024 tiles), 8192 rows 864 against 993;
+// below, dZ of w = 384, 4096 rows (384 tiles) 27 against 20, dW of w = 1024 (256 tiles),
+// 8192 rows 401 against 216.
+bool staged(bool ta, bool tb, int M, int N, int K) {
+  const int64_t tiles = (int64_t)((M + kTile - 1) / kTile) * ((N + kTile - 1) / kTile);
+  return ta || tb ? tiles >= 512 : tiles >= 1024 && K >= 768;
+}
+
 // C = op(A) op(B) (+ bias[col]) (tanh) (* (1 - D^2)): a layer's product with its bias
-// (no operand transposed), or a gradient's (one of them); colsum (FP32, ta only): the
-// column sums of B
+// (no operand transposed), or a gradient's (one of them); colsum (ta only; cols_done
+// tells whether they were formed): the column sums of B
 hipError_t gemm(bool ta, bool tb, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
                 float *C, int ldc, const float *bias, int epi, const float *dact, int ldd, bool bf16,
-                hipStream_t s, float *colsum = nullptr) {
+                hipStream_t s, float *colsum = nullptr, bool *cols_done = nullptr) {
+  if (cols_done) *cols_done = false;
   if ((ta && tb) || (!bf16 && !ta && !tb && (!bias || dact))) return hipErrorInvalidValue;
   if (M <= 0 || N <= 0) return hipSuccess;
-  if (bf16) return gemm_bf16(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epi, dact, ldd, s);
+  if (bf16) return gemm_staged<true>(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epi, dact, ldd, s);
+  if (staged(ta, tb, M, N, K)) return gemm_staged<false>(ta, tb, M, N, K, A, lda, B, ldb, C, ldc, bias, epi, dact, ldd, s);
+  if (cols_done) *cols_done = ta && colsum != nullptr;
   if (ta) return grad_f32<true>(M, N, K, A, lda, B, ldb, C, ldc, dact, ldd, colsum, s);
   if (tb) return grad_f32<false>(M, N, K, A, lda, B, ldb, C, ldc, dact, ldd, nullptr, s);
   return layer_f32(M, N, K, A, lda, B, ldb, C, ldc, bias, epi, s);
@@ -824,11 +858,12 @@ scdg_status scdg_mlp_backward(scdg_mlp *m, const float *w, const float *x, const
     const float *a_prev = l == 0 ? x : c.act + (size_t)(l - 1) * c.max_batch * c.n_hidden;
     const int fi = c.fan_in[l], fo = c.fan_out[l];
     // dW_l = A_{l-1}^T dZ_l  [fi x fo]
-    // and db_l = column sums of dZ_l, from the same product in FP32
+    // and db_l = column sums of dZ_l, from the same product where it forms them
+    bool cols_done = false;
     hipError_t e = scdg::gemm(true, false, fi, fo, batch, a_prev, fi, dz, fo, dw + c.w_off[l], fo, nullptr,
-                              scdg::kEpiNone, nullptr, 0, c.bf16, c.stream, dw + c.b_off[l]);
+                              scdg::kEpiNone, nullptr, 0, c.bf16, c.stream, dw + c.b_off[l], &cols_done);
     if (e != hipSuccess) return SCDG_ERR_HIP;
-    if (c.bf16) {
+    if (!cols_done) {
       hipLaunchKernelGGL(scdg::colsum_partial_kernel, dim3((fo + 255) / 256, scdg::kColChunks), dim3(256), 0,
                          c.stream, dz, batch, fo, c.colpart);
       hipLaunchKernelGGL(scdg::colsum_final_kernel, dim3((fo + 255) / 256), dim3(256), 0, c.stream, c.colpart,
