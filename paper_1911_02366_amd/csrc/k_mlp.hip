@@ -707,10 +707,21 @@ __global__ void apply_kernel(const double *__restrict__ dq_prev, const float *__
     dq[i] = dq_prev[i] + stats[15 + (int)(i % 5)] * (double)y[i];
 }
 
-// dst[r] = src[idx[r]], one value a thread: rows of any width fill the waves (1e6 rows
-// of 5: 24 us, against 240 with a workgroup per row; 1024 of 1250: 7.3 and 8.3 us)
-__global__ void gather_rows_kernel(const float *__restrict__ src, int width, const int32_t *__restrict__ idx,
-                                   int count, float *__restrict__ dst) {
+// dst[r] = src[idx[r]].  Rows of 256 values and more: a workgroup a row, no division
+// (a training step of 1024 rows of 1250 and 625: 1.0 us less); narrower ones: a value a
+// thread, so that they fill the waves (1e6 rows of 5: 24 us, against 240 with a
+// workgroup a row; 1e5 of 64: 14 and 29; 2e4 of 135: 8.9 and 9.9).
+__global__ __launch_bounds__(256) void gather_rows_kernel(const float *__restrict__ src, int width,
+                                                          const int32_t *__restrict__ idx, int count,
+                                                          float *__restrict__ dst) {
+  for (int64_t r = blockIdx.x; r < count; r += gridDim.x) {
+    const float *__restrict__ row = src + (int64_t)idx[r] * width;
+    for (int c = threadIdx.x; c < width; c += 256) dst[r * width + c] = row[c];
+  }
+}
+
+__global__ void gather_values_kernel(const float *__restrict__ src, int width, const int32_t *__restrict__ idx,
+                                     int count, float *__restrict__ dst) {
   const int64_t total = (int64_t)count * width;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -912,8 +923,12 @@ scdg_status scdg_mlp_gather(scdg_mlp *m, const float *src, int32_t width, const 
                             float *dst) {
   if (!m || !src || !idx || !dst || width <= 0 || count < 0) return SCDG_ERR_ARG;
   if (count == 0) return SCDG_OK;
-  hipLaunchKernelGGL(scdg::gather_rows_kernel, dim3(scdg::grid_for((int64_t)count * width)), dim3(256), 0,
-                     m->c.stream, src, width, idx, count, dst);
+  if (width >= 256)
+    hipLaunchKernelGGL(scdg::gather_rows_kernel, dim3((unsigned)std::min(count, 1 << 20)), dim3(256), 0, m->c.stream,
+                       src, width, idx, count, dst);
+  else
+    hipLaunchKernelGGL(scdg::gather_values_kernel, dim3(scdg::grid_for((int64_t)count * width)), dim3(256), 0,
+                       m->c.stream, src, width, idx, count, dst);
   return hip_status(hipGetLastError());
 }
 
