@@ -162,23 +162,10 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc *__restrict__ desc, con
   const int n_full = d.k / BK, nk = (d.k + BK - 1) / BK;
   if (n_full > 0) load(0);
   else load_tail(0);
-  // C += +-A B: the sums start from +-C, whose loads run beside the first slab's
-  // and not after the last product (216 blocks of 1080 with K = 128: 1.51 -> 1.33 ms;
-  // on 128x128 tiles the loads cost the second workgroup of a CU or spill)
-  if (PRE) {
-    const T *__restrict__ c0 = c + (int64_t)m0 * d.ldc + n0;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = min(wn * WTN + j * 16 + (lane & 15), d.n - 1 - n0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = min(wm * WTM + i * 16 + M::row(lane, r), d.m - 1 - m0);
-          acc[i][j][r] = alpha * c0[(uint32_t)(row * d.ldc + col)];
-        }
-      }
-  }
+  // C += +-A B: C's loads run beside the last slab's products, not after them.  (The
+  // sums could start from C instead, but then every product is rounded at C's size:
+  // the inverse of 1080 rows was a third further off.)
+  T old[PRE ? TM : 1][PRE ? TN : 1][4];
   store(0);
   __syncthreads();
   // the K loop is compiled twice: without per-block guards for a wave whose
@@ -217,6 +204,20 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc *__restrict__ desc, con
       store((kt + 1) & 1);
       __syncthreads();
       ++kt;
+    }
+    if constexpr (PRE) {
+      const T *__restrict__ c0 = c + (int64_t)m0 * d.ldc + n0;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int col = min(wn * WTN + j * 16 + (lane & 15), d.n - 1 - n0);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = min(wm * WTM + i * 16 + M::row(lane, r), d.m - 1 - m0);
+            old[i][j][r] = c0[(uint32_t)(row * d.ldc + col)];
+          }
+        }
     }
     products(kt & 1);
     __syncthreads();                           // the epilogue stages in the slabs' memory
@@ -282,7 +283,8 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc *__restrict__ desc, con
         if (row < d.m) {
           T *dst = c + (int64_t)row * d.ldc + col;
           T v = alpha * acc[i][j][r];
-          if (!PRE && beta != T(0)) v += beta * (*dst);
+          if (PRE) v += old[PRE ? i : 0][PRE ? j : 0][r];
+          else if (beta != T(0)) v += beta * (*dst);
           if ((fok >> (4 * j + r)) & 1) v = (T)((double)v + fv[j][r]);
           *dst = v;
         }

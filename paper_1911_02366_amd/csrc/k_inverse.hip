@@ -1197,9 +1197,9 @@ __global__ __launch_bounds__(256, 2) void gj_apply_kernel(T *__restrict__ work, 
   }
   // entries past the edges read the last row's and column's values and are not stored
   T *__restrict__ wo = w + (int64_t)row0 * n + o0;
-  typename M::acc_t acc[4];
+  typename M::acc_t acc[4], old[4];            // added at the end: products are rounded at their own size
 #pragma unroll
-  for (int j = 0; j < 4; ++j) acc[j] = M::zero();
+  for (int j = 0; j < 4; ++j) acc[j] = old[j] = M::zero();
   if (ow > 0 && row0 < n) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1207,7 +1207,7 @@ __global__ __launch_bounds__(256, 2) void gj_apply_kernel(T *__restrict__ work, 
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const T v = wo[min(M::row(lane, r), n - 1 - row0) * n + col];
-        acc[j][r] = diag ? T(0) : v;
+        old[j][r] = diag ? T(0) : v;
       }
     }
   }
@@ -1237,7 +1237,7 @@ __global__ __launch_bounds__(256, 2) void gj_apply_kernel(T *__restrict__ work, 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = M::row(lane, r);
-      if (row0 + i < n && col < ow) wo[i * n + col] = acc[j][r];
+      if (row0 + i < n && col < ow) wo[i * n + col] = old[j][r] + acc[j][r];
     }
   }
 }
