@@ -13,8 +13,8 @@
 //   3. fluxes F_d = f^a_d(q) - f^nu_d(q, g) staged in LDS, one workgroup per element, then
 //        H = J s w_i w_j w_k sum_d (1/w_l) [ sum_a Vw[l][a] F_d(a) + [l = N] Fhat_R - [l = 0] Fhat_L ]
 //      with Vw[l][a] = -w_a D[a][l].
-// Both elements of a face take the same Fhat, so the scheme is conservative to
-// the last bit.  Gradients and face fluxes lie in work arrays component by
+// Both elements of a face take the same Fhat (on curved elements each along its own
+// face vector, which agree to rounding), so the scheme is conservative.  Gradients and face fluxes lie in work arrays component by
 // component within an element (15 x nodes) and a direction (5 x faces), so that
 // consecutive lanes read and write consecutive values.
 //
@@ -162,31 +162,35 @@ __device__ __forceinline__ void flux_adv_normal(const Prim<T> &a, const T q[5], 
   f[4] = un * (q[4] + a.p);
 }
 
-// viscous flux sum_d nv_d f^nu_d(q, g)
-template <class T>
-__device__ __forceinline__ void flux_visc_normal(const T q[5], const T g[15], const double nv[3], const DgParams &P,
-                                                 T f[5]) {
+// viscous fluxes sum_d nv_d f^nu_d(q, g) through S face vectors
+template <int S, class T>
+__device__ __forceinline__ void flux_visc_normal(const T q[5], const T g[15], const double (*nv)[3], const DgParams &P,
+                                                 T (*f)[5]) {
   const Prim<T> a = prim(q, P.gamma);
   const T ir = 1.0 / q[0];
   const T eE = q[4] * ir;
-  T dv[3][3], den = 0.0;
+  T dv[3][3], de[3];
   for (int k = 0; k < 3; ++k) {
     for (int i = 0; i < 3; ++i) dv[i][k] = (g[k * 5 + 1 + i] - a.u[i] * g[k * 5]) * ir;
-    den += nv[k] * ((g[k * 5 + 4] - eE * g[k * 5]) * ir - (a.u[0] * dv[0][k] + a.u[1] * dv[1][k] + a.u[2] * dv[2][k]));
+    de[k] = (g[k * 5 + 4] - eE * g[k * 5]) * ir - (a.u[0] * dv[0][k] + a.u[1] * dv[1][k] + a.u[2] * dv[2][k]);
   }
   const T temp = P.gamma * P.mach2 * a.p / q[0];
   const T mu = (1.0 + P.suth) / (temp + P.suth) * temp * vsqrt(temp);
   const T div = dv[0][0] + dv[1][1] + dv[2][2];
-  f[0] = 0.0;
-  T work = 0.0;
-  for (int i = 0; i < 3; ++i) {
-    T t = 0.0;
-    for (int d = 0; d < 3; ++d) t += nv[d] * (dv[i][d] + dv[d][i]);
-    t = mu * (t - (2.0 / 3.0) * nv[i] * div);
-    f[1 + i] = t * P.inv_re;
-    work += a.u[i] * t;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    f[s][0] = 0.0;
+    T work = 0.0, den = 0.0;
+    for (int k = 0; k < 3; ++k) den += nv[s][k] * de[k];
+    for (int i = 0; i < 3; ++i) {
+      T t = 0.0;
+      for (int d = 0; d < 3; ++d) t += nv[s][d] * (dv[i][d] + dv[d][i]);
+      t = mu * (t - (2.0 / 3.0) * nv[s][i] * div);
+      f[s][1 + i] = t * P.inv_re;
+      work += a.u[i] * t;
+    }
+    f[s][4] = (work + mu * P.gamma / P.prandtl * den) * P.inv_re;
   }
-  f[4] = (work + mu * P.gamma / P.prandtl * den) * P.inv_re;
 }
 
 // cooperative copy of the parameter block into LDS (ends with a barrier)
@@ -202,12 +206,6 @@ __device__ __forceinline__ int nbr_elem(int e, int k, int d, int step) {
   int c[3] = {e % k, (e / k) % k, e / (k * k)};
   c[d] = (c[d] + step + k) % k;
   return c[0] + k * c[1] + k * k * c[2];
-}
-
-__device__ __forceinline__ int node_with(int node, int p, int d, int l) {
-  int c[3] = {node % p, (node / p) % p, node / (p * p)};
-  c[d] = l;
-  return c[0] + p * c[1] + p * p * c[2];
 }
 
 // index of component t of the gradient work arrays at a node
@@ -333,6 +331,7 @@ __global__ __launch_bounds__((PP * PP * PP + 63) / 64 * 64) void lift_curved_ker
 struct DgArgs {
   const double *q, *dq, *g, *dg, *gb, *dgb, *met, *q_s;
   double *face;       // numerical fluxes (of T = Dual: their derivatives), [3][5][faces of a direction]
+  double *face_plus;  // curved elements: those that the faces' plus sides take
   double *r;
   double inv_dt;
   int64_t n_pairs;    // faces of a direction: n_elem P^2
@@ -341,15 +340,19 @@ struct DgArgs {
 enum FaceKind { kFaceBr1 = 0, kFaceSipg = 1, kFaceCurved = 2 };
 
 // The numerical flux of every +xi_D face node, once: Lax-Friedrichs advective
-// minus {{f^nu(q, grad q)}} along the face vector (e_D, or J a^D of the element on
-// the minus side; the plus side's differs in rounding alone), grad q the lifted
+// minus {{f^nu(q, grad q)}} along the face vector (e_D, or J a^D), grad q the lifted
 // gradient, or the broken one with the penalty term sigma f^nu({{q}}, [[q]] e_D),
 // [[q]] = q^+ - q^- taken as a gradient along the normal.  The terms are taken one
 // side's gradient at a time, which keeps the registers of the dual-number form
 // down.
+//   On curved elements each side takes the flux along its own J a^D (face_plus: the
+// plus side's): the two agree to rounding, but in an element's sums the large
+// constant part of the flux cancels by the discrete metric identity of its own face
+// vectors; along the other side's the residual is up to 28% further off.
 template <class T, int PP, int KIND, int D>
 __device__ __forceinline__ void face_flux_body(const DgParams &P, const DgArgs &a, int64_t idx) {
   constexpr int P2 = PP * PP, P3 = P2 * PP, N = PP - 1;
+  constexpr int S = KIND == kFaceCurved ? 2 : 1;   // face vectors: the minus side's, the plus side's
   constexpr int strides[3] = {1, PP, P2};
   const int64_t e = idx / P2;
   const int tt = (int)(idx - e * P2), t1 = tt % PP, t2 = tt / PP;
@@ -358,38 +361,44 @@ __device__ __forceinline__ void face_flux_body(const DgParams &P, const DgArgs &
   const int nr = t1 * S1 + t2 * S2, nl = nr + N * strides[D];
   const int64_t er = nbr_elem((int)e, P.k_elem, D, 1);
   const int64_t il = e * P3 + nl, ir = er * P3 + nr;
-  double nv[3] = {D == 0 ? 1.0 : 0.0, D == 1 ? 1.0 : 0.0, D == 2 ? 1.0 : 0.0};
-  double sn = 1.0;
-  if (KIND == kFaceCurved) {
-    for (int m = 0; m < 3; ++m) nv[m] = a.met[il * 10 + 3 * D + m];
-    sn = sqrt(nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2]);
+  double nv[S][3];
+  if constexpr (KIND == kFaceCurved) {
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      nv[0][m] = a.met[il * 10 + 3 * D + m];
+      nv[1][m] = a.met[ir * 10 + 3 * D + m];
+    }
   }
-  T ql[5], qr[5], fh[5];
+  T ql[5], qr[5], fh[S][5];
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     ql[v] = at<T>(a.q, a.dq, il * 5 + v);
     qr[v] = at<T>(a.q, a.dq, ir * 5 + v);
   }
   const double *gsrc = KIND == kFaceSipg ? a.gb : a.g, *dgsrc = KIND == kFaceSipg ? a.dgb : a.dg;
-  auto visc = [&](const T *qq, const T *gs, T *fv) {
-    if (KIND == kFaceCurved) flux_visc_normal(qq, gs, nv, P, fv);
-    else flux_visc(qq, gs, D, P, fv);
+  auto visc = [&](const T *qq, const T *gs, T (*fv)[5]) {
+    if constexpr (KIND == kFaceCurved) flux_visc_normal<S>(qq, gs, nv, P, fv);
+    else flux_visc(qq, gs, D, P, fv[0]);
   };
   {
-    T gs[15], fv[5];
+    T gs[15], fv[S][5];
 #pragma unroll
     for (int t = 0; t < 15; ++t) gs[t] = at<T>(gsrc, dgsrc, g_at<PP>(e, t, nl));
     visc(ql, gs, fv);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) fh[v] = -0.5 * fv[v];
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) fh[s][v] = -0.5 * fv[s][v];
   }
   {
-    T gs[15], fv[5];
+    T gs[15], fv[S][5];
 #pragma unroll
     for (int t = 0; t < 15; ++t) gs[t] = at<T>(gsrc, dgsrc, g_at<PP>(er, t, nr));
     visc(qr, gs, fv);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) fh[v] -= 0.5 * fv[v];
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) fh[s][v] -= 0.5 * fv[s][v];
   }
   if constexpr (KIND == kFaceSipg) {
     T qm[5], jg[15], fv[5];
@@ -399,30 +408,36 @@ __device__ __forceinline__ void face_flux_body(const DgParams &P, const DgArgs &
       jg[D * 5 + v] = qr[v] - ql[v];
     }
     flux_visc(qm, jg, D, P, fv);
-    for (int v = 0; v < 5; ++v) fh[v] -= P.sigma * fv[v];
+    for (int v = 0; v < 5; ++v) fh[0][v] -= P.sigma * fv[v];
   }
-  {
-    const Prim<T> b = prim(ql, P.gamma), c = prim(qr, P.gamma);
+  const Prim<T> b = prim(ql, P.gamma), c = prim(qr, P.gamma);
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
     T fa[5], un_l = b.u[D], un_r = c.u[D];
+    double sn = 1.0;
     if constexpr (KIND == kFaceCurved) {
+      sn = sqrt(nv[s][0] * nv[s][0] + nv[s][1] * nv[s][1] + nv[s][2] * nv[s][2]);
       const double inv = 1.0 / sn;
-      un_l = (b.u[0] * nv[0] + b.u[1] * nv[1] + b.u[2] * nv[2]) * inv;
-      un_r = (c.u[0] * nv[0] + c.u[1] * nv[1] + c.u[2] * nv[2]) * inv;
-      flux_adv_normal(b, ql, nv, fa);
+      un_l = (b.u[0] * nv[s][0] + b.u[1] * nv[s][1] + b.u[2] * nv[s][2]) * inv;
+      un_r = (c.u[0] * nv[s][0] + c.u[1] * nv[s][1] + c.u[2] * nv[s][2]) * inv;
+      flux_adv_normal(b, ql, nv[s], fa);
     } else {
       flux_adv(ql, D, P.gamma, fa);
     }
-    for (int v = 0; v < 5; ++v) fh[v] += 0.5 * fa[v];
-    if constexpr (KIND == kFaceCurved) flux_adv_normal(c, qr, nv, fa);
+    for (int v = 0; v < 5; ++v) fh[s][v] += 0.5 * fa[v];
+    if constexpr (KIND == kFaceCurved) flux_adv_normal(c, qr, nv[s], fa);
     else flux_adv(qr, D, P.gamma, fa);
-    for (int v = 0; v < 5; ++v) fh[v] += 0.5 * fa[v];
+    for (int v = 0; v < 5; ++v) fh[s][v] += 0.5 * fa[v];
     const T lam_l = vabs(un_l) + vsqrt(P.gamma * b.p / b.rho);
     const T lam_r = vabs(un_r) + vsqrt(P.gamma * c.p / c.rho);
     const T lam = lam_l >= lam_r ? lam_l : lam_r;
-    for (int v = 0; v < 5; ++v) fh[v] -= 0.5 * lam * sn * (qr[v] - ql[v]);
+    for (int v = 0; v < 5; ++v) fh[s][v] -= 0.5 * lam * sn * (qr[v] - ql[v]);
   }
 #pragma unroll
-  for (int v = 0; v < 5; ++v) a.face[(D * 5 + v) * a.n_pairs + idx] = part(fh[v]);
+  for (int v = 0; v < 5; ++v) {
+    a.face[(D * 5 + v) * a.n_pairs + idx] = part(fh[0][v]);
+    if constexpr (KIND == kFaceCurved) a.face_plus[(D * 5 + v) * a.n_pairs + idx] = part(fh[1][v]);
+  }
 }
 
 // blockIdx.y: the direction (a template argument of the body, whose flux code
@@ -466,13 +481,13 @@ __global__ __launch_bounds__((PP * PP * PP + 63) / 64 * 64) void volume_kernel(c
       const Prim<T> b = prim(qn, P.gamma);
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        double nv[3];
-        for (int m = 0; m < 3; ++m) nv[m] = a.met[id * 10 + 3 * i + m];
-        T fa[5], fv[5];
-        flux_adv_normal(b, qn, nv, fa);
-        flux_visc_normal(qn, gn, nv, P, fv);
+        double nv[1][3];
+        for (int m = 0; m < 3; ++m) nv[0][m] = a.met[id * 10 + 3 * i + m];
+        T fa[5], fv[1][5];
+        flux_adv_normal(b, qn, nv[0], fa);
+        flux_visc_normal<1>(qn, gn, nv, P, fv);
 #pragma unroll
-        for (int v = 0; v < 5; ++v) fs[(i * P3 + node) * 5 + v] = part(fa[v] - fv[v]);
+        for (int v = 0; v < 5; ++v) fs[(i * P3 + node) * 5 + v] = part(fa[v] - fv[0][v]);
       }
       mass = a.met[id * 10 + 9];
     } else {
@@ -506,7 +521,7 @@ __global__ __launch_bounds__((PP * PP * PP + 63) / 64 * 64) void volume_kernel(c
       // the +d face of this element, or of its neighbour on the minus side
       const int64_t ef = l == N ? e : nbr_elem((int)e, P.k_elem, d, -1);
       const int t1 = c[d == 0 ? 1 : 0], t2 = c[d == 2 ? 1 : 2];
-      const double *fh = a.face + d * 5 * a.n_pairs + ef * P2 + t1 + PP * t2;
+      const double *fh = (CURVED && l == 0 ? a.face_plus : a.face) + d * 5 * a.n_pairs + ef * P2 + t1 + PP * t2;
       const double sg = l == N ? 1.0 : -1.0;
 #pragma unroll
       for (int v = 0; v < 5; ++v) rd[v] += sg * fh[v * a.n_pairs];
@@ -1141,6 +1156,7 @@ hipError_t launch_operator(const DgContext &c, DgArgs a, hipStream_t s) {
   const int n_elem = c.host.k_elem * c.host.k_elem * c.host.k_elem;
   a.met = c.met;
   a.face = c.g + 15 * c.n_nodes;
+  a.face_plus = c.met ? c.met + 10 * c.n_nodes : nullptr;
   a.n_pairs = (int64_t)n_elem * c.host.p * c.host.p;
   return with_points(c.host.p, [&](auto pc) {
     constexpr int PP = decltype(pc)::value;
@@ -1302,7 +1318,6 @@ scdg_status dg_jacobian_blocks_on(scdg_dg *dg, const JacPlanView &v, const doubl
   hipLaunchKernelGGL(fill_zero_kernel, dim3(fill_grid), dim3(256), 0, s, abi, n_ib);
   hipLaunchKernelGGL(fill_zero_kernel, dim3(fill_grid), dim3(256), 0, s, bb_val, v.nnzb * 25);
   if (hipMemsetAsync(c.jt_flag, 0, sizeof(int32_t), s) != hipSuccess) return fail("flag reset");
-  const int threads = ((p3 + 63) / 64) * 64;
   if (launch_lift(c, q, c.g, nullptr, nullptr, nullptr, nullptr, s) != hipSuccess) return SCDG_ERR_HIP;
   const int64_t n_nodes = (int64_t)n_elem * p3, n_faces = (int64_t)n_elem * 3 * p * p;
   hipLaunchKernelGGL(pj_node_kernel, dim3((unsigned)((n_nodes + 255) / 256)), dim3(256), 0, s, c.dev, q, c.g, c.pj,
@@ -1501,7 +1516,8 @@ scdg_status scdg_dg_set_geometry(scdg_dg *dg, const double *xyz) {
     return SCDG_ERR_ARG;
   }
   ++c.geo_gen;
-  if (!c.met && hipMalloc(&c.met, sizeof(double) * met.size()) != hipSuccess) {
+  // the metric terms, and behind them the plus sides' face fluxes
+  if (!c.met && hipMalloc(&c.met, sizeof(double) * (met.size() + 15 * (c.n_nodes / c.host.p))) != hipSuccess) {
     c.met = nullptr;
     return SCDG_ERR_NOMEM;
   }
