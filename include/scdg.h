@@ -151,23 +151,25 @@ enum { SCDG_COPY = 0, SCDG_BORROW = 1 };
 scdg_status scdg_assemble(scdg_plan *p, const double *aii, const double *aib,
                           const double *abi, const double *bb_val, int32_t flags);
 
-/* Invert every A_ii(e) by Gauss-Jordan elimination with partial pivoting
- * (the paper inverts each interior block with LU routines, Section 3.2), in
- * FP64 or FP32.  A zero pivot is recorded per element (see scdg_factor_info)
+/* Invert every A_ii(e) by Gauss-Jordan elimination with partial pivoting, or with
+ * pivots inside diagonal blocks where those are as safe (scdg_set_inverse_mode; the
+ * paper inverts each interior block with LU routines, Section 3.2), in
+ * FP64 or FP32.  Asynchronous on the plan's stream; a later call in the same precision
+ * and form can be captured.  A zero pivot is recorded per element (see scdg_factor_info)
  * and reported as SCDG_ERR_SINGULAR by scdg_condense. */
 scdg_status scdg_factor(scdg_plan *p, scdg_precision prec);
 /* Where the GMRES cycle runs (paper, Section 4 uses GMRES on the Newton
  * systems; this is an execution choice, same arithmetic):
- *   0  host-driven: one device-to-host transfer and wait per iteration for the
- *      Hessenberg column; Givens rotations on the host (default);
- *   1  device-resident: Hessenberg column, Givens rotations, stopping test and
- *      the next basis vector's scale stay on the device; every kernel of an
- *      Arnoldi step returns at once when a halt flag is set; the host waits once
- *      per restart cycle (true residual);
+ *   0  watched (default): the Hessenberg column, Givens rotations and the stopping
+ *      test are on the device, and the host enqueues one step ahead of the stopping
+ *      flag that it reads;
+ *   1  whole cycles: as 0, but all steps of a restart cycle are enqueued at once;
+ *      every kernel of an Arnoldi step returns at once when the flag is set; the
+ *      host waits once per restart cycle (true residual);
  *   2  as 1, with the m Arnoldi steps captured once into a HIP graph (on a
  *      plan-owned stream) and replayed per cycle on the plan's stream.  The
  *      graph is recaptured when the restart length, preconditioner, factor
- *      precision or the borrowed A_bb pointer change.  Phase timers do not see
+ *      precision, the form of the products or a buffer's address change.  Phase timers do not see
  *      the kernels inside the graph. */
 scdg_status scdg_set_krylov_mode(scdg_plan *p, int32_t mode);
 /* Form of the Schur products S x inside the GMRES solve.  The paper assembles
@@ -194,17 +196,21 @@ scdg_status scdg_set_krylov_mode(scdg_plan *p, int32_t mode);
 scdg_status scdg_set_schur_mode(scdg_plan *p, int32_t mode);
 scdg_status scdg_get_schur_mode(const scdg_plan *p, int32_t *mode);
 
-/* Form of the batched inverse (Gauss-Jordan with partial pivoting, Section 3.2):
+/* Form of the batched inverse (Gauss-Jordan, Section 3.2):
  * 0 automatic (form 3 up to n_i = 400, else form 2); 1 one workgroup per element for the whole elimination, 24- or
  * 32-column panels in LDS; 2 blocked: outer panels of 128 columns whose update
  * of the rest of the block is a batched matrix-core GEMM; 3 resident panel:
  * one workgroup per element holding an outer panel of 48 (FP64; 32 when some
  * n_i exceeds 320) or 64 (FP32) columns in LDS, so the rest of the block is
  * streamed once per outer panel (n_i <= 400, SCDG_ERR_UNSUPPORTED from
- * scdg_factor otherwise).  All
- * forms use the same pivot rule (largest |a| among unused rows, lowest row on
- * ties); rounding differs with the blocking, so near-ties may pick different
- * rows.  SCDG_ERR_ARG for a mode other than 0..3.  scdg_get_inverse_mode
+ * scdg_factor otherwise).
+ *   Pivots: forms 1 and 3 take the largest |a| among a column's unused rows (lowest
+ * row on ties; rounding differs with the blocking, so near-ties may pick different
+ * rows).  Form 2 takes it inside 64 x 64 diagonal blocks, compared on rows scaled by
+ * powers of two, for the elements whose multipliers stay below 4 and whose entries grow
+ * to less than 8 times a row's largest power of two; the other elements are inverted
+ * with whole-column pivots as in the other forms (scdg_inverse_whole_column).
+ *   SCDG_ERR_ARG for a mode other than 0..3.  scdg_get_inverse_mode
  * reports the form used by the last scdg_factor (0 before). */
 scdg_status scdg_set_inverse_mode(scdg_plan *p, int32_t mode);
 scdg_status scdg_get_inverse_mode(const scdg_plan *p, int32_t *mode_used);
@@ -228,7 +234,9 @@ scdg_status scdg_condense(scdg_plan *p);
  * vector, bs: boundary vector (both device). */
 scdg_status scdg_condense_rhs(scdg_plan *p, const double *b, double *bs);
 
-/* Solve S Q_b = b_S: dense LU with partial pivoting of the assembled S, or
+/* Solve S Q_b = b_S: dense LU of the assembled, row-scaled S (pivots inside the
+ * diagonal blocks of 64-column panels while multipliers and entries of U stay below 4,
+ * else partial pivoting over the whole panel, or in every panel), or
  * restarted GMRES(m) with right point-Jacobi and classical Gram-Schmidt with
  * reorthogonalisation (the paper's solvers: direct, and GMRES with a point-
  * Jacobi preconditioner, Section 4).  x0 (boundary vector) may be NULL. */
@@ -468,11 +476,12 @@ scdg_status scdg_dg_jacobian_blocks(scdg_dg *dg, scdg_plan *plan, const double *
  * condensed (scdg_condense) for a Jacobian supplied by the caller, usually at
  * Q_s, and that Jacobian is kept for every iteration of the step (a chord
  * iteration; with FP32 factors the FP64 nonlinear residual drives the
- * refinement).  An iteration is three graphs: the condensed right-hand side
- * and GMRES set-up; one GMRES restart cycle, replayed until a flag in device
- * memory reports the solve finished (the host reads it after each cycle; at
+ * refinement).  An iteration replays captured graphs: the condensed right-hand side
+ * and GMRES set-up; the steps of a GMRES restart cycle, six to a graph, and the cycle's
+ * end, until flags in device memory report the cycle and the solve finished (the host
+ * reads them after each of these graphs; at
  * most `cycles` cycles, after which the iteration goes on with the partial
- * solution); and back-substitution, update and residual.  Within a cycle the
+ * solution); and back-substitution, update and residual.  The
  * kernels of the steps after convergence return at once.  The host reads
  * ||R(Q)|| after each iteration and stops when ||R(Q)|| <= newton_tol ||R(Q_s)||.  The GMRES tolerance of an iteration is
  * clip(forcing * newton_tol * ||R(Q_s)|| / ||R(Q)||, lin_tol, eta_max)

@@ -18,7 +18,7 @@ constexpr int kNewtonPieces = 3 + (63 + kNewtonSegment - 1) / kNewtonSegment;   
 constexpr int kGjOuter = 128;        // outer panel width of the blocked Gauss-Jordan inverse
 constexpr int kDensePanel = 64;       // panel width of the dense LU of S
 constexpr int kKrylovBlocks = 256;    // workgroups (partial sums per value) of the Gram-Schmidt launches
-constexpr int kGjAutoBlocked = 320;  // automatic choice: blocked form above this n_i
+constexpr int kGjAutoBlocked = 320;  // automatic choice where the resident form has no room: blocked above this n_i
 
 // One GEMM problem of a batched launch: C = alpha A B + beta C, row-major with
 // leading dimensions; offsets are element offsets into the three base arrays.
@@ -106,7 +106,7 @@ struct SparseOp {
 };
 
 // GEMM tile configurations (rows x columns of C per workgroup)
-enum { kGemm64x64 = 0, kGemm64x128 = 1, kGemm128x128 = 2, kGemm128x128w8 = 3, kGemmConfigs = 9 };
+enum { kGemm64x64 = 0, kGemm64x128 = 1, kGemm128x128 = 2, kGemmConfigs = 9 };
 
 template <typename T>
 struct DevBuf {
@@ -373,7 +373,6 @@ hipError_t launch_scatter_axpby(int64_t n, double a, const double *x, double b, 
 // second stage alone (out[1] = st[1] when st is given)
 hipError_t launch_norm2(const double *x, int64_t n, double *part, double *out, hipStream_t s);
 hipError_t launch_sum_parts(const double *part, const int32_t *st, double *out, hipStream_t s);
-hipError_t launch_reciprocal(double *x, int64_t n, hipStream_t s);
 hipError_t launch_krylov_gram_schmidt(const double *v, int64_t ld, int nv, double *w, int64_t n, double *part,
                                       double *h1, double *h2, double *norm_part, hipStream_t s,
                                       const int32_t *halt);

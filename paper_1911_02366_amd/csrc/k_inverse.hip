@@ -798,14 +798,14 @@ __global__ __launch_bounds__(L::NT) void gj_resident_kernel(const double *__rest
 }
 
 // ---------------------------------------------------------------------------
-// Blocked form for large blocks, pivots over whole columns (the form after this one
-// is tried first).  Columns are taken in outer panels of
-// kOuter; inside an outer panel, inner panels of NB columns are eliminated
-// by gj_panel_kernel, which updates only the outer panel's other columns.
+// Blocked form for large blocks, pivots over whole columns, for the elements that the
+// form after this one, which goes first, could not take.  Columns are taken in outer
+// panels of kOuter; gj_panel_kernel eliminates one in inner panels of NB columns,
+// updating only the outer panel's other columns.
 // The rest of the matrix then receives the outer panel's transformation at
 // once, as the rank-kOuter update of the same formula,
 //     W[i][j] <- (i pivot row of the outer panel ? 0 : W[i][j]) + sum_c P[i][c] R[c][j],
-// a batched GEMM (W += P R) after gj_outer_gather_kernel has copied the
+// a batched GEMM (W += P R) after the same kernel has copied the
 // transformed outer panel P, gathered its pivot rows R (zero inside the panel)
 // and cleared those rows outside it.  The composition of the inner steps is
 // the Gauss-Jordan transformation of the whole outer panel, so the result is
@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(256) void gj_start_kernel(const double *__restrict_
     for (int j = lane; j < n; j += 64) {
       const T v = (T)a[j];
       w[j] = v;
-      big = fmax(big, fabs(v));                // a NaN is passed over here and found by the growth check
+      big = fmax(big, fabs(v));                // a NaN is passed over here and found by the multipliers
     }
     big = wave_max_dpp(big);
     if (lane == 0) {

@@ -605,12 +605,6 @@ __global__ void fill_kernel(double *__restrict__ y, int64_t n, double v, const i
     y[i] = v;
 }
 
-__global__ void reciprocal_kernel(double *__restrict__ x, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    x[i] = 1.0 / x[i];
-}
-
 __global__ void cast_kernel(const double *__restrict__ src, float *__restrict__ dst, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
@@ -881,12 +875,6 @@ hipError_t launch_scatter_axpby(int64_t n, double a, const double *x, double b, 
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(scatter_axpby_kernel, dim3(grid_for(n)), dim3(kThreads), 0, s, n, a, x, b,
                      yin, map, dst);
-  return hipGetLastError();
-}
-
-hipError_t launch_reciprocal(double *x, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(reciprocal_kernel, dim3(grid_for(n)), dim3(kThreads), 0, s, x, n);
   return hipGetLastError();
 }
 

@@ -1317,8 +1317,9 @@ scdg_status prepare_blocked_inverse(Plan &p) {
 
 // The same for the form with pivots inside diagonal blocks: the panel itself is
 // the left operand, so its columns are left out (a GEMM on either side).  64x64
-// tiles: the inverse of 216 blocks of 1080 takes 18.4 ms with them, 19.2 with
-// 128x128, 20.4 with 64x128 or 128x64 (before the sums started from C: 16.7).
+// tiles: with the plain kernel on each, the inverse of 216 blocks of 1080 takes 18.4 ms
+// with them, 19.2 with 128x128, 20.4 with 64x128 or 128x64; the update kernel, which
+// only 64x64 tiles have room for, makes it 16.5.
 scdg_status prepare_diagonal_inverse(Plan &p) {
   ST_TRY(prepare_gj_common(p));
   if (p.d_gj_state) return SCDG_OK;

@@ -225,8 +225,8 @@ class Plan:
         return info.as_dict() | {"status": st}
 
     def set_krylov_mode(self, mode: str):
-        """'host' (Givens on the host), 'device' (device-resident cycle) or 'graph'
-        (device-resident cycle replayed from a HIP graph)."""
+        """'host' (the host watches each step's stopping flag), 'device' (whole cycles,
+        the host waits once per cycle) or 'graph' (those replayed from a HIP graph)."""
         m = {"host": 0, "device": 1, "graph": 2}[mode]
         self._check(self.lib.scdg_set_krylov_mode(self.handle, m), "scdg_set_krylov_mode")
 
