@@ -814,33 +814,15 @@ __global__ __launch_bounds__(L::NT) void gj_resident_kernel(const double *__rest
 // ---------------------------------------------------------------------------
 constexpr int kOuter = kGjOuter;
 
-// The kernels of this form work on the elements e with redo[e] set (redo null: on all).
-template <typename T>
-__global__ __launch_bounds__(256) void gj_prepare_kernel(const double *__restrict__ src, T *__restrict__ work,
-                                                         const int32_t *__restrict__ n_arr,
-                                                         const int64_t *__restrict__ off_arr,
-                                                         const int64_t *__restrict__ voff_arr,
-                                                         unsigned char *__restrict__ flags,
-                                                         int32_t *__restrict__ info,
-                                                         const int32_t *__restrict__ redo, int32_t *__restrict__ any) {
-  const int e = blockIdx.x;
-  if (redo && !redo[e]) return;
-  if (redo && blockIdx.y == 0 && threadIdx.x == 0) *any = 1;   // every writer stores 1
-  const int n = n_arr[e];
-  const int64_t total = (int64_t)n * n, off = off_arr[e], voff = voff_arr[e];
-  for (int64_t i = blockIdx.y * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.y * blockDim.x) {
-    work[off + i] = (T)src[off + i];
-    if (i < n) flags[voff + i] = 0;
-  }
-  if (blockIdx.y == 0 && threadIdx.x == 0) info[e] = 0;
-}
-
-// One outer panel of an element: its inner panels one after another, then, where
+// One outer panel of an element (before the first: W = A_ii, nothing pivoted): its
+// inner panels one after another, then, where
 // columns lie outside it, the operands of their update:
 //   P[i][c] = W[i][ko + c];  R[c][j] = W[p_c][j] outside the outer panel (0 inside),
 //   and W[p_c][j] = 0 outside the outer panel.
+// For the elements e with redo[e] set, of which *any tells (redo null: for all).
 template <class L>
-__global__ __launch_bounds__(kThreads) void gj_panel_kernel(typename L::T *__restrict__ work,
+__global__ __launch_bounds__(kThreads) void gj_panel_kernel(const double *__restrict__ src,
+                                                            typename L::T *__restrict__ work,
                                                             const int32_t *__restrict__ n_arr,
                                                             const int64_t *__restrict__ off_arr,
                                                             const int64_t *__restrict__ voff_arr,
@@ -849,7 +831,8 @@ __global__ __launch_bounds__(kThreads) void gj_panel_kernel(typename L::T *__res
                                                             typename L::T *__restrict__ pbuf,
                                                             typename L::T *__restrict__ rbuf,
                                                             int32_t *__restrict__ info,
-                                                            const int32_t *__restrict__ redo, int ko) {
+                                                            const int32_t *__restrict__ redo,
+                                                            int32_t *__restrict__ any, int ko) {
   using T = typename L::T;
   constexpr int NB = L::NB, PS = L::PS;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -865,6 +848,16 @@ __global__ __launch_bounds__(kThreads) void gj_panel_kernel(typename L::T *__res
   const int rp = (n + 15) & ~15;
   GjSmem<L> sm(smem, rp);
   const int tid = threadIdx.x;
+  if (ko == 0) {
+    const double *__restrict__ a = src + off_arr[e];
+    for (int64_t i = tid; i < (int64_t)n * n; i += kThreads) w[i] = (T)a[i];
+    for (int i = tid; i < n; i += kThreads) flags[i] = 0;
+    if (tid == 0) {
+      info[e] = 0;
+      if (any) *any = 1;                       // every writer stores 1
+    }
+    __syncthreads();
+  }
   bool used[kRowsPerThread];
 #pragma unroll
   for (int u = 0; u < kRowsPerThread; ++u) {
@@ -997,7 +990,7 @@ __global__ __launch_bounds__(256) void gj_start_kernel(const double *__restrict_
     info[e] = 0;
     flag[e] = 0;
     stop[e] = 0;
-    if (e == 0) stop[gridDim.x] = 0;           // gj_prepare_kernel tells whether a flag was raised
+    if (e == 0) stop[gridDim.x] = 0;           // gj_panel_kernel tells whether a flag was raised
   }
   for (int i = blockIdx.y * 4 + (threadIdx.x >> 6); i < n; i += gridDim.y * 4) {
     const double *__restrict__ a = src + off + (int64_t)i * n;
@@ -1304,17 +1297,16 @@ hipError_t gj_blocked_run(Plan &p, typename L::T *work, typename L::T *out) {
   if (err != hipSuccess) return err;
   const int32_t *redo = p.d_gj_state;
   T *pbuf = static_cast<T *>(p.gj_pbuf), *rbuf = static_cast<T *>(p.gj_rbuf);
-  hipLaunchKernelGGL((gj_prepare_kernel<T>), dim3(p.n_elem, 16), dim3(256), 0, p.stream, p.aii, work, p.d_inv_n,
-                     p.d_inv_off, p.d_gj_voff, p.d_gj_flag, p.d_info, redo,
-                     redo ? p.d_gj_state + 2 * p.n_elem : nullptr);
+  int32_t *any = redo ? p.d_gj_state + 2 * p.n_elem : nullptr;
   for (int s = 0; s * kOuter < p.max_ni; ++s) {
-    hipLaunchKernelGGL((gj_panel_kernel<L>), dim3(p.n_elem), dim3(kThreads), lds, p.stream, work, p.d_inv_n,
-                       p.d_inv_off, p.d_gj_voff, p.d_gj_piv, p.d_gj_flag, pbuf, rbuf, p.d_info, redo, s * kOuter);
+    hipLaunchKernelGGL((gj_panel_kernel<L>), dim3(p.n_elem), dim3(kThreads), lds, p.stream, p.aii, work, p.d_inv_n,
+                       p.d_inv_off, p.d_gj_voff, p.d_gj_piv, p.d_gj_flag, pbuf, rbuf, p.d_info, redo, any,
+                       s * kOuter);
     if (p.gj_ntiles[s] > 0) {
       const GemmDesc *desc = p.d_gj_desc + p.gj_desc_off[s];
       const int32_t *tiles = p.d_gj_tiles + 3 * p.gj_tile_off[s];
       err = redo ? launch_gemm_updates_few(desc, tiles, p.gj_ntiles[s], pbuf, rbuf, work, 1.0, sizeof(T) == 4,
-                                           p.stream, redo, redo + 2 * p.n_elem)
+                                           p.stream, redo, any)
                  : launch_gemm_updates(desc, tiles, p.gj_ntiles[s], pbuf, rbuf, work, 1.0, sizeof(T) == 4, p.stream);
       if (err != hipSuccess) return err;
     }
@@ -1352,7 +1344,10 @@ hipError_t gj_diagonal_run(Plan &p, T *out) {
   T *dinv = static_cast<T *>(p.gj_blk), *rblk = dinv + (int64_t)p.n_elem * kBlk * kBlk;
   T *scale = rblk + (int64_t)p.n_elem * kBlk * kBlk, *rbuf = static_cast<T *>(p.gj_rbuf);
   int32_t *flag = p.d_gj_state, *stop = flag + p.n_elem;
-  hipLaunchKernelGGL((gj_start_kernel<T>), dim3(p.n_elem, 16), dim3(256), 0, p.stream, p.aii, out, p.d_inv_n,
+  // four rows a workgroup, or enough of them to fill the card (8 blocks of 1080 with 16
+  // workgroups each took 150 us)
+  const int rows4 = (p.max_ni + 3) / 4, split = std::min(rows4, std::max(16, 4096 / p.n_elem));
+  hipLaunchKernelGGL((gj_start_kernel<T>), dim3(p.n_elem, split), dim3(256), 0, p.stream, p.aii, out, p.d_inv_n,
                      p.d_inv_off, p.d_gj_voff, scale, p.d_info, flag, stop);
   for (int s = 0; s * kOuter < p.max_ni; ++s) {
     const int ko = s * kOuter;

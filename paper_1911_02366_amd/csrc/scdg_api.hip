@@ -1345,7 +1345,7 @@ scdg_status prepare_diagonal_inverse(Plan &p) {
 // The blocked inverse: pivots inside diagonal blocks, then the whole-column form on
 // the elements whose pivots did not hold.  The device's flags decide, so the call
 // does not wait and a stream under capture takes the same way; with every element
-// held, the second form's launches return at once (20 at 1080 rows).
+// held, the second form's launches return at once (19 at 1080 rows, 4.5 us each).
 // Without room for the first form's blocks the second inverts every element.
 scdg_status blocked_inverse(Plan &p) {
   ST_TRY(prepare_blocked_inverse(p));
