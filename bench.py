@@ -593,7 +593,7 @@ def main() -> int:
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="only copy a 2 GiB FP64 buffer three times (HBM counter calibration)")
     ap.add_argument("--inverse-mode", choices=["auto", "single", "blocked", "resident"], default="auto",
-                    help="form of the batched inverse (auto: resident panel up to n_i = 352, blocked above 320 "
+                    help="form of the batched inverse (auto: resident panel up to n_i = 400, blocked above "
                          "otherwise)")
     ap.add_argument("--learned-guess", action="store_true",
                     help="run the learned-initial-guess time-stepping experiment instead")

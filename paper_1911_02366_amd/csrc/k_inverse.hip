@@ -964,11 +964,11 @@ __global__ __launch_bounds__(kThreads) void gj_readout_kernel(const T *__restric
 // elements flagged.  The host does not look: a call returns at once and can be
 // captured.  The scaling only steers the choice; the values are not scaled.
 //   Bound by memory: a block's sweep reads and writes 128 columns, an outer panel's
-// update the whole block.  216 elements of n = 1080 in FP64: block launches 17 x 45,
-// apply launches 17 x 154 us (3.1 TB/s), rows 9 x 105 us, the GEMMs 11.7 ms (5.4 are
-// bound by C at 4.9 TB/s, 7.1 by the products); the inverse 16.9 ms against 35.7
-// in the whole-column form, whose 60 panel launches took 210 us each.  216 elements
-// of orders 3 to 7: 6.1 against 21 ms.
+// update the whole block.  216 elements of n = 1080 in FP64: block launches 17 x 48,
+// apply launches 17 x 158 us (3.1 TB/s), rows 9 x 105 us, the GEMMs 11.1 ms (the
+// products alone 7.6 at the matrix rate, C alone 7.4 at 4.9 TB/s); the inverse 16.4 ms
+// against 36.6 in the whole-column form by itself, and 35.6 where every element is
+// rejected.  216 elements of orders 3 to 7: 6.1 against 21 ms.
 // ---------------------------------------------------------------------------
 constexpr int kBlk = 64;
 constexpr int kBlkPad = kBlk + 1;
