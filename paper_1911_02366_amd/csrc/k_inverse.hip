@@ -113,8 +113,9 @@ __device__ void gj_eliminate(GjSmem<L> &sm, int n, int kb, int nbw, bool (&used)
     for (int u = 0; u < kRowsPerThread; ++u) {
       const int i = tid + u * kThreads;
       if (i < n && !used[u]) {
-        const double v = fabs((double)pnl[i * PS + c]);
-        if (v > best) {
+        double v = fabs((double)pnl[i * PS + c]);
+        if (v != v) v = INFINITY;              // a NaN wins and is reported: an unused row is always found,
+        if (v > best) {                        // so that the pivot rows stay a permutation
           best = v;
           bi = i;
         }
